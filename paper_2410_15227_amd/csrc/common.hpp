@@ -121,6 +121,7 @@ struct Ctx {
   std::vector<PairsDev *> scratch_batch;  // pair lists of batched calls that do not keep them
   BlockPool pool;                         // blocks of freed retained pair lists
   int n_cu = 0, exact_per_cu = 0;  // compute units; resident Exact workgroups per CU
+  int exact64_per_cu = 0;          // the same of the binary64 edge kernel
   bool autotune = false;
   std::map<int, TuneChoice> tuned;  // by floor(log2(pairs)) of the Exact launch
   // A second stream (default priority) for work that can overlap the

@@ -35,7 +35,10 @@
 //     a^2 = d^2 + p^2,
 // with coefficients that depend on (|d|, p) only, joined continuously at
 // U = 1.  Two evaluation paths:
-//   binary64: every step in binary64 with the math library's functions;
+//   binary64: every step in binary64, by the edge-parallel kernel with
+//     polynomial cores of the math library's accuracy, or one lane per pair
+//     with the library's functions (pairs the edge kernel leaves, contexts
+//     with a workspace cap, work counting);
 //   mixed: edge geometry in binary32; atan, asinh and square roots from
 //     binary32 polynomial cores and seeds with binary64 range reduction and
 //     assembly (atan within 4.7e-9, log within 7.3e-10 relative);
@@ -192,6 +195,92 @@ struct MathMixed {
   static __device__ inline double sqrt_(double v) { return sqrt_mixed(v); }
   static __device__ inline double rcp(double v) { return rcp_mixed(v); }
 };
+
+// Binary64 cores of the binary64 edge kernel: the reductions of the mixed
+// cores with binary64 polynomials and quotients.  They take a third of the
+// math library's instructions (no operand scaling, special cases or second
+// word), which is what bounds that kernel: lengths here are ratios to h, far
+// from the ends of the exponent range, and a term that is not finite sends
+// its pair to the math library's kernel.
+// 1/x: the hardware's seed (2^-24) and two Newton steps.
+__device__ inline double rcp64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+// num / den with the quotient's residual added (within 1 ulp).
+__device__ inline double div64(double num, double den) {
+  const double r = rcp64(den);
+  const double q = num * r;
+  return fma(fma(-den, q, num), r, q);
+}
+// sqrt(v), v > 0: coupled Newton steps of sqrt and half its inverse from the
+// hardware's seed, then the residual of the square (within 1 ulp).
+__device__ inline double sqrt64(double v) {
+  const double y = __builtin_amdgcn_rsq(v);
+  double g = v * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  return fma(fma(-g, g, v), h, g);
+}
+// 1/sqrt(v), v > 0: two Newton steps from the hardware's seed.
+__device__ inline double rsqrt64(double v) {
+  double y = __builtin_amdgcn_rsq(v);
+  y = fma(0.5 * y, fma(-v * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-v * y, y, 1.0), y);
+}
+// atan2(y, x): atan(s) = s + s^3 P(s^2) after the octant reduction of
+// atan_mixed, P of degree 10 interpolated at the Chebyshev points of
+// [0, tan^2(pi/8)] (fit_cores.py; P within 3.2e-17).
+__device__ inline double atan2_64(double y, double x) {
+  const double ay = fabs(y), ax = fabs(x);
+  const bool small = ay <= 0.41421356237309503 * ax;
+  const bool large = ay >= 2.414213562373095 * ax;
+  const double num = small ? ay : (large ? -ax : ay - ax);
+  const double den = small ? ax : (large ? ay : ay + ax);
+  const double base = small ? 0.0 : (large ? kHalfPi : kQuarterPi);
+  const double s = div64(num, den);
+  const double z = s * s;
+  double A = -0.019176887119062257;
+  A = fma(A, z, 0.03923165829558719);
+  A = fma(A, z, -0.0508544973794026);
+  A = fma(A, z, 0.0585814891280221);
+  A = fma(A, z, -0.06664511447381948);
+  A = fma(A, z, 0.07692183190826087);
+  A = fma(A, z, -0.09090904578123903);
+  A = fma(A, z, 0.11111111015256361);
+  A = fma(A, z, -0.14285714284666542);
+  A = fma(A, z, 0.1999999999999552);
+  A = fma(A, z, -0.3333333333333333);
+  const double r = base + fma(s * z, A, s);
+  return copysign(x < 0.0 ? kPi - r : r, y);
+}
+// log(num / den), num, den > 0, as log_ratio_mixed: 2 atanh(t) = 2t + t^3
+// B(t^2), B of degree 6 at the Chebyshev points of [0, (3 - 2 sqrt 2)^2]
+// (fit_cores.py; B within 3.2e-16, that is 4.6e-18 of the logarithm).
+__device__ inline double log_ratio64(double num, double den) {
+  int e = __builtin_amdgcn_frexp_exp(num) - __builtin_amdgcn_frexp_exp(den);
+  double mn = __builtin_amdgcn_frexp_mant(num);  // [0.5, 1)
+  const double md = __builtin_amdgcn_frexp_mant(den);
+  if (mn < 0.70710678118654752 * md) {
+    mn *= 2.0;
+    e -= 1;
+  } else if (mn > 1.4142135623730950 * md) {
+    mn *= 0.5;
+    e += 1;
+  }
+  const double t = div64(mn - md, mn + md);
+  const double t2 = t * t;
+  double B = 0.14616449685043403;
+  B = fma(B, t2, 0.15331721600556042);
+  B = fma(B, t2, 0.18182889125261723);
+  B = fma(B, t2, 0.2222221113479508);
+  B = fma(B, t2, 0.28571428625975487);
+  B = fma(B, t2, 0.39999999999899505);
+  B = fma(B, t2, 0.666666666666667);
+  return fma((double)e, kLn2, fma(t * t2, B, 2.0 * t));
+}
 
 // ------------------------------------------------------------- one edge
 struct EdgeCount {
@@ -376,6 +465,15 @@ __device__ inline double from_fixed(unsigned long long a) {
   return ((double)hi * 0x1p32 + (double)lo) * 0x1p-46;
 }
 
+// The same in units of 2^-57 for the binary64 edge kernel (a unit below the
+// rounding of the terms themselves): the part above 2^-46 and its exact
+// remainder are each rounded by the constant.
+__device__ inline unsigned long long to_fixed57(double v) {
+  const double t = fma(v, 0x1p46, kFixMagic);
+  const double r = fma(t - kFixMagic, -0x1p-46, v);
+  return (fixed_from(t) << 11) + fixed_from(fma(r, 0x1p57, kFixMagic));
+}
+__device__ inline double from_fixed57(unsigned long long a) { return from_fixed(a) * 0x1p-11; }
 
 // instance holding global chunk `chunk` (chunk0: first chunk of each
 // instance, ascending, n_inst + 1 entries)
@@ -420,15 +518,10 @@ __device__ inline bool disk_within_2h(double xr0, double xr1, double xr2, double
 }
 
 // ------------------------------------------------------- binary64 kernel
-__global__ void __launch_bounds__(256) k_exact_fp64(int64_t P, const int32_t *pair_c, const int32_t *pair_p,
-                                                   const double *xyz, const double *hh, const double *gen,
-                                                   const int64_t *cfo, const int64_t *fvo, const double4 *fplane,
-                                                   const double4 *fsphere, const double *fvpos, double *w_out,
-                                                   int64_t *counters) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= P) return;
-  const int64_t c = pair_c[k];
-  const int64_t i = pair_p[k];
+// One pair in binary64 with the math library, every face from this side.
+__device__ __forceinline__ double pair_fp64(int64_t c, int64_t i, const double *xyz, const double *hh, const double *gen,
+                            const int64_t *cfo, const int64_t *fvo, const double4 *fplane, const double4 *fsphere,
+                            const double *fvpos, int64_t *counters) {
   const double h = hh[i];
   const double ih = 1.0 / h;
   const double xr0 = xyz[3 * i] - gen[3 * c], xr1 = xyz[3 * i + 1] - gen[3 * c + 1],
@@ -454,8 +547,37 @@ __global__ void __launch_bounds__(256) k_exact_fp64(int64_t P, const int32_t *pa
   }
   double S = inside ? 1.0 : 0.0;
   if (inside && on_boundary) S = boundary_S(f0, f1, fplane, fvo, fvpos, xr0, xr1, xr2);
-  w_out[k] = S - acc;
   if (counters) flush_counters(counters, f1 - f0, K);
+  return S - acc;
+}
+
+// Every pair of an instance, one lane each: calls whose workspace cap leaves
+// no room for the edge kernel's records, and work counting.
+__global__ void __launch_bounds__(256) k_exact_fp64(int64_t P, const int32_t *pair_c, const int32_t *pair_p,
+                                                   const double *xyz, const double *hh, const double *gen,
+                                                   const int64_t *cfo, const int64_t *fvo, const double4 *fplane,
+                                                   const double4 *fsphere, const double *fvpos, double *w_out,
+                                                   int64_t *counters) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= P) return;
+  w_out[k] = pair_fp64(pair_c[k], pair_p[k], xyz, hh, gen, cfo, fvo, fplane, fsphere, fvpos, counters);
+}
+
+// The pairs the binary64 edge kernel leaves: a particle on the cell's
+// boundary or within 1e-4 h of an edge's line, more than 64 faces or 256 candidate edges, or a term that is
+// not finite.
+__global__ void __launch_bounds__(256) k_exact_fp64_list(const int64_t *list, const int32_t *n_list,
+                                                         const ExactInst *__restrict__ insts,
+                                                         const int64_t *__restrict__ chunk0, int n_inst) {
+  const int n = *n_list;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+    const int64_t gid = list[t];
+    const int ins = inst_of(chunk0, n_inst, gid >> 6);
+    const ExactInst &I = insts[ins];
+    const int64_t k = gid - chunk0[ins] * 64;
+    I.w[k] = pair_fp64(I.pair_c[k], I.pair_p[k], I.xyz, I.hh, I.gen, I.cfo, I.fvo, I.fplane, I.fsphere, I.fvpos,
+                       nullptr);
+  }
 }
 
 // ---------------------------------------------------------- mixed kernel
@@ -470,6 +592,11 @@ constexpr double kOnPlane = 1e-20;
 // fan's terms there vary on the scale sqrt(d^2 + p^2), so the binary32
 // rounding of the foot point and edge frame is amplified by its inverse.
 constexpr float kEdgeNear = 1e-2f;
+// The same for the binary64 edge kernel, whose pairs then go to the one-lane
+// kernel: on an edge or a vertex the terms rest on the rounding of each
+// face's d and p, which another order of operations would change at will.
+// About one pair in 3e7 of a turbulent cloud's grid.
+constexpr double kEdgeNear64 = 1e-4;
 // A cell smaller than this fraction of h (R_c < 0.25 h) is evaluated as on
 // the binary64 path (binary64 geometry and functions): its faces are small
 // and, seen from a particle far out in the support, their terms cancel far
@@ -687,6 +814,12 @@ struct Piece64 {
   static __device__ inline double sqrt_(double v) { return sqrt(v); }
 };
 
+struct Piece64Core {
+  static __device__ inline double atan2_(double y, double x) { return atan2_64(y, x); }
+  static __device__ inline double log_ratio(double num, double den) { return log_ratio64(num, den); }
+  static __device__ inline double sqrt_(double v) { return sqrt64(v); }
+};
+
 // F(v) - F(u) over [u, v] inside one regime with coefficients c, from
 // differences: phi(v) - phi(u) and beta(v) - beta(u) as one angle each
 // (atan2 of the tangent-difference numerator and denominator, scaled by
@@ -772,6 +905,10 @@ __device__ inline double item_value(const float4 it, int mode, EdgeCount &cnt) {
   const double ad = (double)fabsf(it.x), p = (double)fabsf(it.y), tA = (double)it.z, tB = (double)it.w;
   const double v = piece_of<PieceMixed>(ad, p, tA, tB, mode, cnt);
   return ((it.x < 0.0f) != (it.y < 0.0f)) ? -v : v;
+}
+__device__ inline double item_value(const double4 it, int mode, EdgeCount &cnt) {
+  const double v = piece_of<Piece64Core>(fabs(it.x), fabs(it.y), it.z, it.w, mode, cnt);
+  return ((it.x < 0.0) != (it.y < 0.0)) ? -v : v;
 }
 
 // |d| int [H(U) - H(|d|)] dphi over the fan of one edge (p > 0, tA < tB),
@@ -1229,10 +1366,61 @@ struct EdgeData {  // what one lane reads for its edge: face record and edge geo
   int rec;  // index of the face record
 };
 
+// The binary64 edge kernel's face record: everything in binary64, the edge
+// geometry formed from the vertices (a frame kept per vertex slot would
+// take 32 more bytes a slot of every grid).
+struct __align__(16) FaceRec64 {
+  double px, py, pz;  // foot point about the generator
+  double d;           // signed |d| / h
+  double dhs;         // -sign(d) |d| H(|d|)
+  double ih;          // 1/h of the pair
+  uint32_t slot;      // bits 0-23: first vertex slot - the chunk's first; 24-29: lane of the pair
+  uint32_t face;      // bits 0-23: face - the chunk's first; 24-31: vertices of the face
+  uint32_t pad[2];
+};
+static_assert(sizeof(FaceRec64) == 64, "records are addressed as index << 6");
+struct EdgeData64 {
+  FaceRec64 fc;
+  double ax, ay, az, bx, by, bz, nx, ny, nz;
+  int rec;
+};
+
+// The two precisions of the edge-parallel kernel.
+//   Geo32 (mixed path): four waves per SIMD (128 VGPRs; 4 workgroups of 39 KB
+//     LDS per CU): the few values that spill are the chunk's and the
+//     fetch's, stored and reloaded outside the edge walk and the queue
+//     evaluation.  A region holds the most records a chunk can have.
+//   Geo64 (binary64 path): LDS and registers (binary64 items and edge data)
+//     leave three waves per SIMD.  A region holds 2,048 records of the about
+//     530 a chunk has on a turbulent cloud's grid; pairs beyond them are
+//     listed for the one-lane kernel.  It issues about 340 instructions per
+//     64 lanes and pair (45 edges walked, 30 pieces), nearly all binary64:
+//     5.6 ms of issue in the 8.0 ms of a 65,521-particle turbulent cloud's
+//     10.2M pairs, which took the one-lane kernel 41 ms (its lanes diverge
+//     over faces, edges and regimes, and its library functions scale and
+//     test every operand); 0.50 against 2.5 ms at 4,096 uniform particles.
+struct Geo32 {
+  using Item = float4;
+  using Rec = FaceRec;
+  using Edge = EdgeData;
+  using Loc = uint32_t;
+  static constexpr bool k64 = false;
+  static constexpr int kEntries = kEntryCap, kPerSimd = 4;
+};
+struct Geo64 {
+  using Item = double4;
+  using Rec = FaceRec64;
+  using Edge = EdgeData64;
+  using Loc = uint2;
+  static constexpr bool k64 = true;
+  static constexpr int kEntries = 2048, kPerSimd = 3;
+};
+
 struct Sphere {
   double x, y, z, r;
 };
 
+template <class G>
 struct EdgeWave {  // per-wavefront LDS
   union {
     double4 wpl[64];  // cull and face list: window of the chunk's faces: plane
@@ -1251,7 +1439,7 @@ struct EdgeWave {  // per-wavefront LDS
   unsigned char wnv[64];
   unsigned long long acc[64];  // per pair: the total of its own face records
   // items: edge data, and the record (bits 0-11) and mode (bits 12-13)
-  float4 q[kQueue];
+  typename G::Item q[kQueue];
   uint16_t o[kQueue];
   // open face records, slot r mod kRing: the fixed-point sum of record r's
   // terms, whether an edge of it comes within 2h, and whether an edge sees
@@ -1301,6 +1489,19 @@ __device__ inline FaceRec load_rec(gptr<FaceRec> base, int rec) {
   return r;
 }
 
+__device__ inline FaceRec64 load_rec(gptr<FaceRec64> base, int rec) {
+  const gptr<double> q = (gptr<double>)((gptr<char>)base + ((uint32_t)rec << 6));
+  const gptr<uint32_t> u = (gptr<uint32_t>)(q + 6);
+  return FaceRec64{q[0], q[1], q[2], q[3], q[4], q[5], u[0], u[1], {}};
+}
+// where a record's edges and face lie
+__device__ inline uint32_t load_loc(gptr<FaceRec> base, int rec) {
+  return *(gptr<uint32_t>)((gptr<char>)base + ((uint32_t)rec << 5) + 28);
+}
+__device__ inline uint2 load_loc(gptr<FaceRec64> base, int rec) {
+  const gptr<uint32_t> u = (gptr<uint32_t>)((gptr<char>)base + ((uint32_t)rec << 6) + 48);
+  return make_uint2(u[0], u[1]);
+}
 
 __device__ inline uint64_t lanes_in(int lo, int hi) {  // bits [lo, hi), 0 <= lo <= hi <= 64
   const uint64_t a = hi >= 64 ? ~0ull : ((1ull << hi) - 1ull);
@@ -1310,15 +1511,23 @@ __device__ inline uint64_t lanes_in(int lo, int hi) {  // bits [lo, hi), 0 <= lo
 
 // Evaluate the first n (<= 64) queued items and add them to their records;
 // move the rest (at most kQueue - 64) to the front.  Returns the new length.
-__device__ inline int drain(EdgeWave &L, int len, int n, int lane, EdgeCount &cnt) {
+template <class G>
+__device__ inline int drain(EdgeWave<G> &L, int len, int n, int lane, gptr<typename G::Rec> frg, EdgeCount &cnt) {
   if (lane < n) {
     const int o = L.o[lane];
     const double r = item_value(L.q[lane], o >> 12, cnt);
-    atomicAdd(&L.racc[o & (kRing - 1)], to_fixed(r));
+    if constexpr (G::k64) {
+      if (fabs(r) < 32.0)
+        atomicAdd(&L.racc[o & (kRing - 1)], to_fixed57(r));
+      else
+        L.redo[(load_loc(frg, o & 0xfff).x >> 24) & 63u] = 1;
+    } else {
+      atomicAdd(&L.racc[o & (kRing - 1)], to_fixed(r));
+    }
   }
   const int rest = len - n;
   const bool ha = lane < rest, hb = lane + 64 < rest;
-  float4 a = {}, b = {};
+  typename G::Item a = {}, b = {};
   uint16_t oa = 0, ob = 0;
   if (ha) {
     a = L.q[n + lane];
@@ -1341,19 +1550,20 @@ __device__ inline int drain(EdgeWave &L, int len, int n, int lane, EdgeCount &cn
   return rest;
 }
 
-template <bool kCount>
-// Four waves per SIMD (128 VGPRs; 4 workgroups of 39 KB LDS per CU): the
-// few values that spill are the chunk's and the fetch's, stored and reloaded
-// outside the edge walk and the queue evaluation.
-__global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
+template <class G, bool kCount>
+__global__ void __launch_bounds__(64 * kFlatWaves, G::kPerSimd) k_exact_edges(
     const ExactInst *__restrict__ insts, const int64_t *__restrict__ chunk0, int n_inst, int per_fetch,
-    int64_t *counters, FaceRec *faces, int32_t *rec_slot, int32_t *next_chunk, int64_t *redo, int32_t *n_redo) {
-  __shared__ EdgeWave lds[kFlatWaves];
+    int64_t *counters, typename G::Rec *faces, int32_t *rec_slot, int32_t *next_chunk, int64_t *redo,
+    int32_t *n_redo) {
+  using Rec = typename G::Rec;
+  using Edge = typename G::Edge;
+  using Loc = typename G::Loc;
+  __shared__ EdgeWave<G> lds[kFlatWaves];
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  EdgeWave &L = lds[wid];
+  EdgeWave<G> &L = lds[wid];
   const int64_t wave = (int64_t)blockIdx.x * kFlatWaves + wid;
-  FaceRec *const fr = faces + wave * kEntryCap;
-  int32_t *const rtw = rec_slot + wave * kEntryCap;
+  Rec *const fr = faces + wave * G::kEntries;
+  int32_t *const rtw = rec_slot + wave * G::kEntries;
   const int64_t n_chunks = chunk0[n_inst];
   Counters K;
   int64_t nfaces = 0;
@@ -1384,7 +1594,10 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
     // the vector-memory counter and never hold up waits on LDS traffic
     const gptr<float4> edgeA = (gptr<float4>)I.edgeA, edgeE = (gptr<float4>)I.edgeE, edgeM = (gptr<float4>)I.edgeM;
     const gptr<int32_t> fcode = (gptr<int32_t>)I.fcode;
-    const bool shared = I.gift != nullptr;  // the same for the whole wave
+    const gptr<double> fvpos = (gptr<double>)I.fvpos;
+    // the same for the whole wave; the binary64 path takes every face from
+    // its own side
+    const bool shared = !G::k64 && I.gift != nullptr;
     const int64_t P = I.P;
     const int64_t chunk = gchunk - chunk0[ins];
     const int64_t k = chunk * 64 + lane;
@@ -1396,7 +1609,7 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
     const int64_t F0 = uniform64(cfo[pair_c[chunk * 64]]), F1 = uniform64(cfo[pair_c[k_last] + 1]);
     // vertex slots of the chunk's faces, kept relative to the first in 24 bits
     const int64_t VB = uniform64(fvo[F0]);
-    const bool wide = fvo[F1] - VB > kSlotSpan;
+    const bool wide = fvo[F1] - VB > kSlotSpan || (G::k64 && F1 - F0 > kSlotSpan);
     uint64_t mask = 0, farmask = 0;
     int nsurv = 0, nedge = 0;
     bool inside = true, on_boundary = false, again = false;
@@ -1415,7 +1628,7 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
       f1 = cfo[c + 1];
       nfaces += f1 - f0;
       if (f1 - f0 > kMaxFaces) again = true;
-      if ((double)((gptr<float>)I.radius)[c] < kSmallCell * h) again = true;  // binary64 geometry
+      if (!G::k64 && (double)((gptr<float>)I.radius)[c] < kSmallCell * h) again = true;  // binary64 geometry
     }
     for (int64_t wb = F0; wb < F1; wb += 64) {
       {
@@ -1461,8 +1674,8 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
           // a foot point beyond the sphere by kFarFoot h is outside the
           // polygon and clear of its vertices
           const double rf = sp.r + kFarFoot * h;
-          const bool far = rho2 > rf * rf;
-          const bool deg = near & (fabs(dist * ih) < kOnPlane);
+          const bool far = !G::k64 & (rho2 > rf * rf);
+          const bool deg = !G::k64 & near & (fabs(dist * ih) < kOnPlane);
           again |= deg;
           const bool keep = near & !deg & (L.wnv[j] > 0);  // a face without edges adds nothing
           mask |= (uint64_t)keep << (wb + j - f0);
@@ -1492,7 +1705,18 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
       const int ns = ((gptr<int32_t>)I.cslots)[c];
       for (int q = 0; q < ns; ++q) I.gift[gbl + (int64_t)q * gnl] = 0;
     }
-    const int e_off = wave_scan_excl(nsurv, lane);
+    int e_off = wave_scan_excl(nsurv, lane);
+    if constexpr (G::kEntries < kEntryCap) {
+      // pairs past the region's end (all that follow the first such pair)
+      if (__ballot(e_off + nsurv > G::kEntries)) {
+        if (e_off + nsurv > G::kEntries) {
+          again = true;
+          mask = 0;
+          nsurv = nedge = 0;
+        }
+        e_off = wave_scan_excl(nsurv, lane);
+      }
+    }
     const int x_off = wave_scan_excl(nedge, lane);
     // wave-uniform counts in scalar registers (the edge walk's loop bound)
     const int n_edge = __builtin_amdgcn_readlane(x_off + nedge, 63);
@@ -1531,21 +1755,35 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
             m &= m - 1;
             const double4 pl = L.wpl[j];
             const double dist = pl.w - (pl.x * xr0 + pl.y * xr1 + pl.z * xr2);
-            // |d| rounded to binary32, like the rest of the face's geometry
-            const float df = (float)(dist * ih);
-            FaceRec rec;
-            rec.px = (float)(xr0 + dist * pl.x);
-            rec.py = (float)(xr1 + dist * pl.y);
-            rec.pz = (float)(xr2 + dist * pl.z);
-            rec.df = df;
-            const double dh = dH((double)fabsf(df));
-            rec.dhs = (df > 0.0f ? -dh : dh) * 0x1p46;
-            rec.ihf = (float)ih;
-            // a face whose foot point is far outside it: its angle part is
-            // exactly 0, so its edges add no angle terms
-            const uint32_t fb = (uint32_t)((farmask >> bit) & 1ull) << 31;
-            rec.slot = (uint32_t)(L.wvs[j] - VB) | ((uint32_t)lane << 24) | fb;
-            fr[e] = rec;
+            if constexpr (G::k64) {
+              Rec rec;
+              rec.px = xr0 + dist * pl.x;
+              rec.py = xr1 + dist * pl.y;
+              rec.pz = xr2 + dist * pl.z;
+              rec.d = dist * ih;
+              const double dh = dH(fabs(rec.d));
+              rec.dhs = rec.d > 0.0 ? -dh : dh;
+              rec.ih = ih;
+              rec.slot = (uint32_t)(L.wvs[j] - VB) | ((uint32_t)lane << 24);
+              rec.face = (uint32_t)(wb + j - F0) | ((uint32_t)L.wnv[j] << 24);
+              fr[e] = rec;
+            } else {
+              // |d| rounded to binary32, like the rest of the face's geometry
+              const float df = (float)(dist * ih);
+              Rec rec;
+              rec.px = (float)(xr0 + dist * pl.x);
+              rec.py = (float)(xr1 + dist * pl.y);
+              rec.pz = (float)(xr2 + dist * pl.z);
+              rec.df = df;
+              const double dh = dH((double)fabsf(df));
+              rec.dhs = (df > 0.0f ? -dh : dh) * 0x1p46;
+              rec.ihf = (float)ih;
+              // a face whose foot point is far outside it: its angle part is
+              // exactly 0, so its edges add no angle terms
+              const uint32_t fb = (uint32_t)((farmask >> bit) & 1ull) << 31;
+              rec.slot = (uint32_t)(L.wvs[j] - VB) | ((uint32_t)lane << 24) | fb;
+              fr[e] = rec;
+            }
             if (shared) rtw[e] = L.wtw[j];  // the face's gift slot, or -1
             atomicOr(&L.sb[start >> 6], 1ull << (start & 63));
             ++e;
@@ -1567,7 +1805,7 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
     uint32_t magic_hi;
     asm volatile("s_mov_b32 %0, 0x43380000" : "=s"(magic_hi));
     const double magic = __hiloint2double((int)magic_hi, 0);
-    const gptr<FaceRec> frg = (gptr<FaceRec>)fr;
+    const gptr<Rec> frg = (gptr<Rec>)fr;
     // Close records [done, upto): each one's total -- the sum of its terms,
     // or, when no edge of it came within 2h, its exact angle sum 2 pi [foot
     // point inside] times its factor (a face clear of the support adds
@@ -1578,9 +1816,13 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
         const int r = done + lane;
         if (r < upto) {
           const int sl = r & (kRing - 1);
-          const FaceRec rc = load_rec(frg, r);
-          const long long T = L.rint[sl] ? (long long)L.racc[sl]
-                                         : (L.rnin[sl] ? 0ll : (long long)fixed_from(fma(rc.dhs, 2.0 * kPi, magic)));
+          const Rec rc = load_rec(frg, r);
+          unsigned long long all_round;  // the exact angle sum of a foot point inside
+          if constexpr (G::k64)
+            all_round = to_fixed57(rc.dhs * (2.0 * kPi));
+          else
+            all_round = fixed_from(fma(rc.dhs, 2.0 * kPi, magic));
+          const long long T = L.rint[sl] ? (long long)L.racc[sl] : (L.rnin[sl] ? 0ll : (long long)all_round);
           const int ow = (int)((rc.slot >> 24) & 63u);
           atomicAdd(&L.acc[ow], (unsigned long long)T);
           if (shared) {
@@ -1597,7 +1839,7 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
     };
     // Evaluate batch [b, b + 64) from the data d fetched for it; `walked`
     // is the first record with an edge past the batch (n_rec after the last).
-    auto batch = [&](int b, const EdgeData &d, int walked) {
+    auto batch = [&](int b, const Edge &d, int walked) {
       const int g = b + lane;
       const bool live = g < n_edge;
       // The batch touches records [first, last]; their ring slots must not
@@ -1608,40 +1850,75 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
         const int first = __builtin_amdgcn_readfirstlane(d.rec);
         const int last = __builtin_amdgcn_readlane(d.rec, 63);
         if (last >= done + kRing) {
-          while (qn > 0) qn = drain(L, qn, min(qn, 64), lane, K.fd);
+          while (qn > 0) qn = drain<G>(L, qn, min(qn, 64), lane, frg, K.fd);
           retire(first);
         }
       }
       const int sl = d.rec & (kRing - 1);
-      const FaceRec &fc = d.fc;
-      const float4 EA = d.ea, EE = d.ee, EM = d.em;
+      const Rec &fc = d.fc;
       // Branch-free: nearly every lane has a live edge of positive length at
       // a nonzero distance, so every lane does the arithmetic (the clamped
       // loads keep it finite) and the tests only select what is kept.
       const int owner = (int)((fc.slot >> 24) & 63u);
-      const bool far = (fc.slot & kFarBit) != 0u;
-      const float dx = fc.px - EA.x, dy = fc.py - EA.y, dz = fc.pz - EA.z;
-      const float p = (dx * EM.x + dy * EM.y + dz * EM.z) * fc.ihf;
-      // an edge of positive length whose line passes within 1e-2 h of the
-      // particle (d^2 + p^2), or whose foot point lies on its line (p = 0),
-      // needs binary64 geometry: the pair goes to the redo kernel
-      const bool act = live & (EA.w > 0.0f);
-      const bool degen = act & ((p == 0.0f) | (fmaf(fc.df, fc.df, p * p) < kEdgeNear * kEdgeNear));
-      if (degen) L.redo[owner] = 1;
-      const bool ok = act & !degen;
-      // the foot point is outside the record's polygon if any edge sees it
-      // on its outer side
-      if (ok & (p < 0.0f)) L.rnin[sl] = 1;
-      const float tA = -(dx * EE.x + dy * EE.y + dz * EE.z) * fc.ihf;
-      const float tB = fmaf(EA.w, fc.ihf, tA);
-      const double ap = (double)fabsf(p), dA = (double)tA, dB = (double)tB;
-      const double ad = (double)fabsf(fc.df);
-      // the angle term -dh (phi_B - phi_A), negated when the edge and the
-      // face are oriented oppositely (p and d of unequal signs): the record's
-      // factor takes the sign bit of p (p != 0 here) and feeds one fma
-      const double f = __hiloint2double(__double2hiint(fc.dhs) ^ (int)(__float_as_uint(p) & 0x80000000u),
-                                        __double2loint(fc.dhs));
-      if (ok & !far) atomicAdd(&L.racc[sl], fixed_from(fma(MathMixed::span(ap, dA, dB), f, magic)));
+      double ap, dA, dB, ad;
+      bool ok;
+      typename G::Item it;  // d, p, tA, tB
+      if constexpr (G::k64) {
+        const double dx = fc.px - d.ax, dy = fc.py - d.ay, dz = fc.pz - d.az;
+        const double lx = d.bx - d.ax, ly = d.by - d.ay, lz = d.bz - d.az;
+        const double len2 = lx * lx + ly * ly + lz * lz;
+        const double il = rsqrt64(len2);
+        const double ex = lx * il, ey = ly * il, ez = lz * il;
+        // in-plane normal of the edge pointing into the polygon: n x e
+        const double mx = d.ny * ez - d.nz * ey, my = d.nz * ex - d.nx * ez, mz = d.nx * ey - d.ny * ex;
+        const double p = (dx * mx + dy * my + dz * mz) * fc.ih;
+        ap = fabs(p);
+        ad = fabs(fc.d);
+        const bool act = live & (len2 != 0.0);
+        const bool degen = act & (fma(ad, ad, p * p) < kEdgeNear64 * kEdgeNear64);
+        if (degen) L.redo[owner] = 1;
+        ok = act & !degen & (p != 0.0);
+        // a foot point on an edge line: that edge adds 0, and the face keeps
+        // the sum of its other edges' terms
+        if (act & (p == 0.0)) L.rint[sl] = 1;
+        if (ok & (p < 0.0)) L.rnin[sl] = 1;
+        dA = -(dx * ex + dy * ey + dz * ez) * fc.ih;
+        dB = ((d.bx - fc.px) * ex + (d.by - fc.py) * ey + (d.bz - fc.pz) * ez) * fc.ih;
+        it = make_double4(fc.d, p, dA, dB);
+        const double v = atan2_64(ap * (dB - dA), fma(dA, dB, ap * ap)) * (p < 0.0 ? -fc.dhs : fc.dhs);
+        if (ok) {
+          if (fabs(v) < 32.0)
+            atomicAdd(&L.racc[sl], to_fixed57(v));
+          else
+            L.redo[owner] = 1;
+        }
+      } else {
+        const float4 EA = d.ea, EE = d.ee, EM = d.em;
+        const bool far = (fc.slot & kFarBit) != 0u;
+        const float dx = fc.px - EA.x, dy = fc.py - EA.y, dz = fc.pz - EA.z;
+        const float p = (dx * EM.x + dy * EM.y + dz * EM.z) * fc.ihf;
+        // an edge of positive length whose line passes within 1e-2 h of the
+        // particle (d^2 + p^2), or whose foot point lies on its line (p = 0),
+        // needs binary64 geometry: the pair goes to the redo kernel
+        const bool act = live & (EA.w > 0.0f);
+        const bool degen = act & ((p == 0.0f) | (fmaf(fc.df, fc.df, p * p) < kEdgeNear * kEdgeNear));
+        if (degen) L.redo[owner] = 1;
+        ok = act & !degen;
+        // the foot point is outside the record's polygon if any edge sees it
+        // on its outer side
+        if (ok & (p < 0.0f)) L.rnin[sl] = 1;
+        const float tA = -(dx * EE.x + dy * EE.y + dz * EE.z) * fc.ihf;
+        const float tB = fmaf(EA.w, fc.ihf, tA);
+        ap = (double)fabsf(p), dA = (double)tA, dB = (double)tB;
+        ad = (double)fabsf(fc.df);
+        // the angle term -dh (phi_B - phi_A), negated when the edge and the
+        // face are oriented oppositely (p and d of unequal signs): the record's
+        // factor takes the sign bit of p (p != 0 here) and feeds one fma
+        const double f = __hiloint2double(__double2hiint(fc.dhs) ^ (int)(__float_as_uint(p) & 0x80000000u),
+                                          __double2loint(fc.dhs));
+        if (ok & !far) atomicAdd(&L.racc[sl], fixed_from(fma(MathMixed::span(ap, dA, dB), f, magic)));
+        it = make_float4(fc.df, p, tA, tB);
+      }
       // within 2h somewhere on [tA, tB], and crossing U = 1 (squares, no
       // roots; bitwise logic, so that no test becomes a branch)
       const double a2 = ad * ad + ap * ap;
@@ -1656,7 +1933,6 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
         K.ne_int += integ;
       }
       // one item per edge within 2h, two for a range crossing U = 1
-      const float4 it = make_float4(fc.df, p, tA, tB);
       const uint64_t m1 = __ballot(integ), m2 = __ballot(integ && cross);
       if (integ) {
         L.rint[sl] = 1;
@@ -1671,7 +1947,7 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
       }
       qn += __popcll(m1) + __popcll(m2);
       wave_sync();
-      while (qn >= 64) qn = drain(L, qn, 64, lane, K.fd);
+      while (qn >= 64) qn = drain<G>(L, qn, 64, lane, frg, K.fd);
       // records before both the next batch and the oldest queued item are
       // complete: close them a full round at a time
       int front = walked;
@@ -1709,42 +1985,68 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
     // and 32-bit offsets (a chunk spans fewer than 2^24 slots, a wave holds
     // 4096 records)
     const gptr<float4> cA = edgeA + VB, cE = edgeE + VB, cM = edgeM + VB;
-    auto fetch = [&](int rec, int vq, uint32_t slot, EdgeData &d) {
+    auto fetch = [&](int rec, int vq, Loc loc, Edge &d) {
       d.rec = rec;
       d.fc = load_rec(frg, rec);
-      const uint32_t v = (slot & 0xffffffu) + (uint32_t)vq;
-      d.ea = load4(cA, v);
-      d.ee = load4(cE, v);
-      d.em = load4(cM, v);
+      if constexpr (G::k64) {
+        const uint32_t v0 = loc.x & 0xffffffu, q1 = (uint32_t)vq + 1u == loc.y >> 24 ? 0u : (uint32_t)vq + 1u;
+        const gptr<double> A = fvpos + 3 * (VB + v0 + (uint32_t)vq), B = fvpos + 3 * (VB + v0 + q1);
+        const gptr<double> N = (gptr<double>)(fplane + F0 + (loc.y & 0xffffffu));
+        d.ax = A[0], d.ay = A[1], d.az = A[2];
+        d.bx = B[0], d.by = B[1], d.bz = B[2];
+        d.nx = N[0], d.ny = N[1], d.nz = N[2];
+      } else {
+        const uint32_t v = (loc & 0xffffffu) + (uint32_t)vq;
+        d.ea = load4(cA, v);
+        d.ee = load4(cE, v);
+        d.em = load4(cM, v);
+      }
     };
-    auto slot_of = [&](int rec) { return *(gptr<uint32_t>)((gptr<char>)frg + ((uint32_t)rec << 5) + 28); };
+    auto slot_of = [&](int rec) { return load_loc(frg, rec); };
     // one turn: evaluate batch b from `cur` while batch b + 64 is fetched
     // into `nxt` (record and slot in r, q, sl) and the record and slot of
     // batch b + 128 are found (into rn, qn, sn).  The loop below alternates
     // the roles of the two sets, so no loaded register is copied.
-    auto turn = [&](int b, const EdgeData &cur, EdgeData &nxt, int r, int q, uint32_t sl, int &rn, int &qn_,
-                    uint32_t &sn) {
+    auto turn = [&](int b, const Edge &cur, Edge &nxt, int r, int q, Loc sl, int &rn, int &qn_, Loc &sn) {
       locate(b + 128, rn, qn_);
       sn = slot_of(rn);
       fetch(r, q, sl, nxt);
       batch(b, cur, b + 64 < n_edge ? __builtin_amdgcn_readfirstlane(r) : n_rec);
     };
-    EdgeData dX{}, dY{};
+    Edge dX{}, dY{};
     int rX = 0, qX = 0, rY = 0, qY = 0;
-    uint32_t sX = 0, sY = 0;
-    if (n_edge > 0) {
-      int r0, q0;
-      locate(0, r0, q0);
-      fetch(r0, q0, slot_of(r0), dX);
-      locate(64, rX, qX);
-      sX = slot_of(rX);
+    Loc sX{}, sY{};
+    if constexpr (G::k64) {
+      // only the record and slot are found a batch ahead: edge data in
+      // flight would take 35 registers a batch, which spill at three waves
+      // per SIMD (11.1 ms on 10.2M pairs, against 8.4 ms) and leave room for
+      // two without (8.9 ms)
+      int r = 0, q = 0;
+      if (n_edge > 0) {
+        locate(0, r, q);
+        sX = slot_of(r);
+      }
+      for (int b = 0; b < n_edge; b += 64) {
+        fetch(r, q, sX, dX);
+        locate(b + 64, r, q);
+        sX = slot_of(r);
+        batch(b, dX, b + 64 < n_edge ? __builtin_amdgcn_readfirstlane(r) : n_rec);
+      }
+    } else {
+      if (n_edge > 0) {
+        int r0, q0;
+        locate(0, r0, q0);
+        fetch(r0, q0, slot_of(r0), dX);
+        locate(64, rX, qX);
+        sX = slot_of(rX);
+      }
+      for (int b = 0; b < n_edge; b += 128) {
+        turn(b, dX, dY, rX, qX, sX, rY, qY, sY);
+        if (b + 64 >= n_edge) break;
+        turn(b + 64, dY, dX, rY, qY, sY, rX, qX, sX);
+      }
     }
-    for (int b = 0; b < n_edge; b += 128) {
-      turn(b, dX, dY, rX, qX, sX, rY, qY, sY);
-      if (b + 64 >= n_edge) break;
-      turn(b + 64, dY, dX, rY, qY, sY, rX, qX, sX);
-    }
-    while (qn > 0) qn = drain(L, qn, min(qn, 64), lane, K.fd);
+    while (qn > 0) qn = drain<G>(L, qn, min(qn, 64), lane, frg, K.fd);
     retire(n_rec);
     wave_sync();
     if (valid && !again && L.redo[lane] == 0) {
@@ -1753,7 +2055,8 @@ __global__ void __launch_bounds__(64 * kFlatWaves, 4) k_exact_edges(
         I.w[k] = __longlong_as_double((long long)L.acc[lane]);
         I.wflag[k] = inside ? kFlagInside : 0;
       } else {
-        I.w[k] = (inside ? 1.0 : 0.0) - kInv4Pi * from_fixed(L.acc[lane]);
+        const double own = G::k64 ? from_fixed57(L.acc[lane]) : from_fixed(L.acc[lane]);
+        I.w[k] = (inside ? 1.0 : 0.0) - kInv4Pi * own;
       }
     } else if (valid) {
       if (kCount) ++K.n64;  // a pair left to the binary64 kernel
@@ -1856,8 +2159,26 @@ static void launch_gather(Ctx &ctx, const std::vector<ExactJob> &jobs, const Gif
 static void exact_occupancy(Ctx &ctx) {
   if (ctx.n_cu != 0) return;
   SPH_HIP(hipDeviceGetAttribute(&ctx.n_cu, hipDeviceAttributeMultiprocessorCount, ctx.device));
-  SPH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&ctx.exact_per_cu, k_exact_edges<false>, 64 * kFlatWaves, 0));
+  SPH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&ctx.exact_per_cu, k_exact_edges<Geo32, false>,
+                                                       64 * kFlatWaves, 0));
+  SPH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&ctx.exact64_per_cu, k_exact_edges<Geo64, false>,
+                                                       64 * kFlatWaves, 0));
+  ctx.exact64_per_cu = std::max(ctx.exact64_per_cu, 1);
   ctx.exact_per_cu = std::max(ctx.exact_per_cu, 1);
+}
+
+// The binary64 path over every pair, one lane each.
+static void exact_fp64_direct(const std::vector<ExactJob> &jobs, int64_t *ctr, hipStream_t s) {
+  for (const auto &j : jobs) {
+    const TessDev &t = *j.t;
+    const PartDev &p = *j.p;
+    PairsDev &P = *j.P;
+    if (P.n_pairs == 0) continue;
+    k_exact_fp64<<<(unsigned)div_up(P.n_pairs, 256), 256, 0, s>>>(P.n_pairs, P.pair_c, P.pair_p, p.xyz, p.h, t.gen,
+                                                                  t.cell_face_off, t.face_vtx_off, t.fplane,
+                                                                  t.fsphere, t.fvpos, P.w, ctr);
+    SPH_LAUNCH_CHECK();
+  }
 }
 
 void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int precision, hipStream_t s,
@@ -1905,7 +2226,7 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
     }
     k_zero_i32<<<1, 64, 0, s>>>(next, kCtrInts);
     SPH_LAUNCH_CHECK();
-    k_exact_edges<false><<<(unsigned)grid, 64 * kFlatWaves, 0, s>>>(d_inst, tab->chunk0, n_inst, pf, nullptr, faces,
+    k_exact_edges<Geo32, false><<<(unsigned)grid, 64 * kFlatWaves, 0, s>>>(d_inst, tab->chunk0, n_inst, pf, nullptr, faces,
                                                                    rtw, next, redo, next + kRedoCtr);
     SPH_LAUNCH_CHECK();
     k_exact_mixed_list<<<(unsigned)(ctx.n_cu * 4), 256, 0, s>>>(redo, next + kRedoCtr, d_inst, tab->chunk0, n_inst,
@@ -1917,20 +2238,19 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   int64_t *ctr = ctx.counting ? ctx.d_counters : nullptr;
   if (ctr) SPH_HIP(hipMemsetAsync(ctr, 0, 8 * sizeof(int64_t), s));
   if (total == 0) return;
-  if (precision == SPHMAP_PREC_FP64) {
+  const bool fp64 = precision == SPHMAP_PREC_FP64;
+  // The binary64 edge kernel takes the mixed path's kinds of scratch (work
+  // list, face records).  In a context with a workspace cap the one-lane
+  // kernel runs, which needs none, so that every call the cap admits stays
+  // admitted: 41 against 8.0 ms for the 10.2M pairs of a 65,521-particle
+  // turbulent cloud.  It also counts the work, and its weights are then
+  // replaced.
+  if (fp64 && (ctr || ctx.ws.limit)) {
     KernelTimer kt(&ctx, "exact_integral", s);
-    for (const auto &j : jobs) {
-      const TessDev &t = *j.t;
-      const PartDev &p = *j.p;
-      PairsDev &P = *j.P;
-      if (P.n_pairs == 0) continue;
-      k_exact_fp64<<<(unsigned)div_up(P.n_pairs, 256), 256, 0, s>>>(P.n_pairs, P.pair_c, P.pair_p, p.xyz, p.h, t.gen,
-                                                                    t.cell_face_off, t.face_vtx_off, t.fplane,
-                                                                    t.fsphere, t.fvpos, P.w, ctr);
-      SPH_LAUNCH_CHECK();
-    }
+    exact_fp64_direct(jobs, ctr, s);
     kt.done();
-    return;
+    if (ctx.ws.limit) return;
+    ctr = nullptr;
   }
   // instance table: each instance's pairs start at a fresh 64-pair chunk
   const int n_inst = (int)jobs.size();
@@ -1938,10 +2258,10 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   ExactInst *host = (ExactInst *)stage;
   int64_t *c0 = (int64_t *)(stage + ((n_inst * sizeof(ExactInst) + 63) & ~(size_t)63));
   c0[0] = 0;
-  const GiftPlan G = gift_plan(ctx, ctx.arena, jobs, false, 0.0, s);
+  const GiftPlan G = fp64 ? GiftPlan() : gift_plan(ctx, ctx.arena, jobs, false, 0.0, s);
   const bool shared = G.any;
   for (int k = 0; k < n_inst; ++k) {
-    host[k] = inst_of_job(jobs[k], &G, k);
+    host[k] = inst_of_job(jobs[k], fp64 ? nullptr : &G, k);
     c0[k + 1] = c0[k] + div_up(jobs[k].P->n_pairs, 64);
   }
   ExactInst *d_inst = ctx.arena.get<ExactInst>("flat_insts", n_inst);
@@ -1954,6 +2274,20 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   const int64_t n_chunks = c0[n_inst];
   int32_t *next = ctx.arena.get<int32_t>("flat_next", kCtrInts);  // work counters, redo count
   int64_t *redo = ctx.arena.get<int64_t>("flat_redo", total);
+  if (fp64) {
+    const int64_t grid = std::min<int64_t>((int64_t)n_cu * ctx.exact64_per_cu, div_up(n_chunks, kFlatWaves));
+    FaceRec64 *faces = ctx.arena.get<FaceRec64>("flat_faces", grid * kFlatWaves * Geo64::kEntries);
+    k_zero_i32<<<1, 64, 0, s>>>(next, kCtrInts);
+    SPH_LAUNCH_CHECK();
+    KernelTimer kt(&ctx, "exact_integral", s);
+    k_exact_edges<Geo64, false><<<(unsigned)grid, 64 * kFlatWaves, 0, s>>>(d_inst, d_c0, n_inst, 1, nullptr, faces,
+                                                                          nullptr, next, redo, next + kRedoCtr);
+    SPH_LAUNCH_CHECK();
+    k_exact_fp64_list<<<(unsigned)n_cu, 256, 0, s>>>(redo, next + kRedoCtr, d_inst, d_c0, n_inst);
+    SPH_LAUNCH_CHECK();
+    kt.done();
+    return;
+  }
   auto launch = [&](int blocks_per_cu, int per_fetch) {
     const int64_t grid = std::min<int64_t>((int64_t)n_cu * std::min(blocks_per_cu, per_cu), div_up(n_chunks, kFlatWaves));
     const int64_t waves = grid * kFlatWaves;
@@ -1964,7 +2298,7 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
     SPH_LAUNCH_CHECK();
     kz.done();
     KernelTimer kt(&ctx, "exact_integral", s);
-    (ctr ? k_exact_edges<true> : k_exact_edges<false>)<<<(unsigned)grid, 64 * kFlatWaves, 0, s>>>(
+    (ctr ? k_exact_edges<Geo32, true> : k_exact_edges<Geo32, false>)<<<(unsigned)grid, 64 * kFlatWaves, 0, s>>>(
         d_inst, d_c0, n_inst, per_fetch, ctr, faces, rtw, next, redo, next + kRedoCtr);
     SPH_LAUNCH_CHECK();
     kt.done();
@@ -2044,6 +2378,9 @@ size_t exact_workspace_bytes(Ctx &ctx, int64_t n_pairs) {
   exact_occupancy(ctx);
   const int64_t grid = std::min<int64_t>((int64_t)ctx.n_cu * ctx.exact_per_cu, div_up(div_up(n_pairs, 64), kFlatWaves));
   const int64_t waves = std::max<int64_t>(grid, 1) * kFlatWaves;
+  // (the binary64 path's regions are smaller: fewer waves, and 128 KB each)
+  static_assert(Geo64::kPerSimd <= Geo32::kPerSimd && Geo64::kEntries * sizeof(FaceRec64) <= kEntryCap * sizeof(FaceRec),
+                "the mixed path's bound covers both");
   // face records, their totals and gift slots per resident wave; per pair
   // the redo list, the flags and its gifts (at most kGiftBound slots a pair
   // on average: a cell evaluates about half its faces' shares)

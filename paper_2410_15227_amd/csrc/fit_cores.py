@@ -16,9 +16,17 @@ the function itself.
          left by splitting off the binary exponent and folding the mantissa
          into [1/sqrt(2), sqrt(2)]), Q of degree 3; log and asinh use it.
 
+The binary64 cores (atan2_64, log_ratio64) have the same forms with degrees
+10 and 6: P and Q are interpolated at the Chebyshev points of the reduced
+range in exact rational arithmetic (their Taylor series have rational
+coefficients) and rounded once.
+
 Run: python fit_cores.py   (prints the coefficients in the order Horner
 evaluates them, highest degree first, and the achieved errors)."""
 from __future__ import annotations
+
+import math
+from fractions import Fraction
 
 import numpy as np
 from scipy.optimize import linprog
@@ -103,6 +111,37 @@ def achieved(P32, Q32, n=200001):
     return ea, eh
 
 
+def interpolate64(taylor, b, degree, terms=60):
+    """(coefficients highest degree first, largest error) of the polynomial
+    through g(z) = sum_k taylor(k) z^k at the Chebyshev points of [0, b]."""
+    n = degree + 1
+    x = [Fraction(b) * Fraction((1.0 + math.cos(math.pi * (2 * i + 1) / (2 * n))) / 2.0) for i in range(n)]
+
+    def g(z):
+        return sum(taylor(k) * z ** k for k in range(terms))
+
+    c = [g(z) for z in x]
+    for j in range(1, n):  # divided differences
+        for i in range(n - 1, j - 1, -1):
+            c[i] = (c[i] - c[i - 1]) / (x[i] - x[i - j])
+    poly = [Fraction(0)]
+    for i in range(n - 1, -1, -1):  # Newton's form to powers of z
+        poly = [(poly[k - 1] if k else 0) - x[i] * (poly[k] if k < len(poly) else 0) for k in range(len(poly) + 1)]
+        poly[0] += c[i]
+    poly = poly[:n]
+    grid = [Fraction(b) * k / 200 for k in range(201)]
+    err = max(abs(sum(a * z ** k for k, a in enumerate(poly)) - g(z)) for z in grid)
+    return [float(a) for a in poly[::-1]], float(err)
+
+
+def fit_atan64(degree=10):
+    return interpolate64(lambda k: Fraction((-1) ** (k + 1), 2 * k + 3), math.tan(math.pi / 8) ** 2, degree)
+
+
+def fit_atanh64(degree=6):
+    return interpolate64(lambda k: Fraction(2, 2 * k + 3), (3.0 - 2.0 * math.sqrt(2.0)) ** 2, degree)
+
+
 if __name__ == "__main__":
     P, e1 = fit_atan()
     Q, e2 = fit_atanh()
@@ -110,3 +149,5 @@ if __name__ == "__main__":
     print("atanh Q (highest degree first):", ", ".join(f"{float(c)!r}f" for c in Q), f"  (LP bound {e2:.2e})")
     ea, eh = achieved(P, Q)
     print(f"achieved relative error with binary32 coefficients: atan {ea:.2e}, 2 atanh {eh:.2e}")
+    for name, (C, e) in (("atan", fit_atan64()), ("atanh", fit_atanh64())):
+        print(f"binary64 {name} (highest degree first):", ", ".join(repr(c) for c in C), f"  (within {e:.1e})")
