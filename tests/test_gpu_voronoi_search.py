@@ -1,0 +1,60 @@
+"""The device Voronoi builder where its neighbour search and its cells' limits
+work hardest, against the oracle's brute-force cells: a few sites far from a
+dense clump (grid cells are descended into; cells that outgrow 64 planes on
+the way are built again), clumps within clumps, flat and long boxes, a
+lattice, two to five sites, and the same under a workspace cap (a coarser
+site grid).  Volumes and radii within 1e-11 of the cell's own scale, as in
+the builder's other tests."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def sites(name):
+    rng = np.random.default_rng(12)
+    lo, hi = np.zeros(3), np.ones(3)
+    if name == "clump":
+        g = np.concatenate([0.5 + 0.01 * (rng.random((700, 3)) - 0.5), rng.random((12, 3))])
+    elif name == "nested":
+        g = np.concatenate([0.3 + 10.0 ** -k * (rng.random((120, 3)) - 0.5) for k in range(1, 4)] + [rng.random((40, 3))])
+    elif name in ("shell", "thick"):  # a lone site facing many: most are cut away by nearer ones
+        u = rng.standard_normal((600, 3))
+        g = np.concatenate([[[0.5, 0.5, 0.5]], 0.5 + u / np.linalg.norm(u, axis=1)[:, None] * rng.uniform(0.2 if name == "shell" else 0.12, 0.45, (600, 1))])
+    elif name == "flat":
+        hi = np.array([1.0, 0.8, 0.02])
+        g = rng.random((600, 3)) * hi
+    elif name == "long":
+        lo, hi = np.array([-3.0, 1.0, 0.0]), np.array([97.0, 1.5, 0.4])
+        g = lo + rng.random((500, 3)) * (hi - lo)
+    elif name == "lattice":
+        a = (np.arange(7) + 0.5) / 7.0
+        g = np.stack(np.meshgrid(a, a, a), -1).reshape(-1, 3)
+    else:
+        g = rng.random((int(name), 3))
+    return g, lo, hi
+
+
+@pytest.mark.parametrize("cap", [0, 8 << 30])
+@pytest.mark.parametrize("name", ["clump", "nested", "shell", "thick", "flat", "long", "lattice", "2", "5"])
+def test_cells_match_oracle(name, cap, oracle):
+    import paper_2410_15227_amd as pkg
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("case:", name, cap, flush=True)
+    g, lo, hi = sites(name)
+    want = oracle.voronoi(g, lo, hi)
+    ctx = pkg.Context(0, workspace_bytes=cap)
+    if np.diff(want["cell_face_off"]).max() > 64:  # 58 neighbours and the box
+        with pytest.raises(pkg.SphmapError, match="58 neighbours"):
+            pkg.build_voronoi(ctx, g, lo, hi, n_lloyd=0)
+        ctx.close()
+        return
+    dt, out = pkg.build_voronoi(ctx, g, lo, hi, n_lloyd=0)
+    vol, rad = (a.cpu().numpy() for a in dt.cell_info())
+    assert np.array_equal(out.cpu().numpy(), g)
+    assert np.max(np.abs(vol - want["volume"]) / want["volume"]) < 1e-11
+    assert abs(vol.sum() / np.prod(hi - lo) - 1.0) < 1e-11
+    dt.free()
+    ctx.close()
