@@ -154,8 +154,20 @@ __global__ void __launch_bounds__(kBlock) k_scan_reduce(const int64_t *in, int64
   if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
+// boff: the blocks' offsets, or with `sums` their sums, which every block then
+// adds up itself: at most kScanSelf of them, 2 microseconds of reading
+// instead of another launch.
+constexpr int64_t kScanSelf = 1024;
 __global__ void __launch_bounds__(kBlock) k_scan_apply(const int64_t *in, int64_t *out, int64_t n,
-                                                       const int64_t *boff, bool write_total) {
+                                                       const int64_t *boff, bool sums, bool write_total) {
+  int64_t before = 0;
+  if (sums) {
+    int64_t p = 0;
+    for (int64_t b = threadIdx.x; b < blockIdx.x; b += kBlock) p += boff[b];
+    (void)block_exclusive_scan<int64_t>(p, &before);
+  } else if (boff) {
+    before = boff[blockIdx.x];
+  }
   const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
   int64_t v[kItems];
   int64_t s = 0;
@@ -167,7 +179,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_apply(const int64_t *in, int64_
   }
   int64_t tot;
   int64_t ex = block_exclusive_scan<int64_t>(s, &tot);
-  int64_t off = (boff ? boff[blockIdx.x] : 0) + ex;
+  int64_t off = before + ex;
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
     int64_t i = base + j;
@@ -186,96 +198,267 @@ void scan_exclusive_i64(Arena &ar, const int64_t *in, int64_t *out, int64_t n, b
   }
   int64_t nb = div_up(n, kTile);
   if (nb == 1) {
-    k_scan_apply<<<1, kBlock, 0, s>>>(in, out, n, nullptr, write_total);
+    k_scan_apply<<<1, kBlock, 0, s>>>(in, out, n, nullptr, false, write_total);
     SPH_LAUNCH_CHECK();
     return;
   }
   // per-level scratch, named by size so recursion levels do not collide
   std::string tag = "scan_bsum_" + std::to_string(nb);
   int64_t *bsum = ar.get<int64_t>(tag, nb + 1);
-  int64_t *boff = ar.get<int64_t>(tag + "_off", nb + 1);
   k_scan_reduce<<<(unsigned)nb, kBlock, 0, s>>>(in, n, bsum);
   SPH_LAUNCH_CHECK();
-  scan_exclusive_i64(ar, bsum, boff, nb, false, s);
-  k_scan_apply<<<(unsigned)nb, kBlock, 0, s>>>(in, out, n, boff, write_total);
+  const bool self = nb <= kScanSelf;
+  int64_t *boff = bsum;
+  if (!self) {
+    boff = ar.get<int64_t>(tag + "_off", nb + 1);
+    scan_exclusive_i64(ar, bsum, boff, nb, false, s);
+  }
+  k_scan_apply<<<(unsigned)nb, kBlock, 0, s>>>(in, out, n, boff, self, write_total);
   SPH_LAUNCH_CHECK();
 }
 
 // ------------------------------------------------------------ radix sort
+// Stable LSD sort of (key, value) pairs by up to 8 key bits a pass.  Tiles of
+// 2048 items; a wavefront takes its 512 in input order, 64 at a time, and a
+// lane finds the lanes that share its digit from one ballot per digit bit.
+// What bounds a pass at the sizes sorted here (up to a few million items) is
+// its launches, so there are few: a sort that fits one workgroup's LDS runs
+// all its passes in one launch, one of up to 64 tiles takes two a pass (each
+// tile adds up the tiles before it itself), a longer one three.  (4-bit
+// passes of histogram, scan and scatter took 24 to 40 launches for 30 bits:
+// 100 us of a 512-particle mapping's 518.)
 namespace {
 
-constexpr int kRadixBits = 4;
+constexpr int kRadixBits = 8;
 constexpr int kBins = 1 << kRadixBits;
+constexpr int kSelfTiles = 64;  // tiles up to which a tile adds up those before it
+constexpr int kOneItems = 4096;  // items one workgroup sorts
+constexpr int kOneThreads = 1024;
 
+// The lanes of the wave that hold the same digit as this one (of the valid lanes).
+__device__ inline uint64_t digit_peers(bool valid, unsigned d, int rb) {
+  uint64_t peers = __ballot(valid);
+  for (int b = 0; b < rb; ++b) {
+    const bool set = (d >> b) & 1u;
+    const uint64_t bal = __ballot(set);
+    peers &= set ? bal : ~bal;
+  }
+  return peers;
+}
+
+// counts [digit][tile], or [tile][digit] for the tiles that add up themselves
 template <typename K>
-__global__ void __launch_bounds__(kBlock) k_radix_hist(const K *keys, int64_t n, int shift, int64_t *hist,
-                                                       int64_t nblocks) {
-  __shared__ int cnt[kBins];
-  if (threadIdx.x < kBins) cnt[threadIdx.x] = 0;
+__global__ void __launch_bounds__(kBlock) k_radix_hist(const K *keys, int64_t n, int shift, int rb, uint32_t *hist,
+                                                       int64_t nt, bool by_tile) {
+  __shared__ unsigned h[kBins];
+  const int nd = 1 << rb;
+  if ((int)threadIdx.x < nd) h[threadIdx.x] = 0u;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * kTile;
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
-    int64_t i = base + (int64_t)j * kBlock + threadIdx.x;
-    if (i < n) atomicAdd(&cnt[(int)((keys[i] >> shift) & (kBins - 1))], 1);
+    const int64_t i = base + (int64_t)j * kBlock + threadIdx.x;
+    if (i < n) atomicAdd(&h[(unsigned)(keys[i] >> shift) & (unsigned)(nd - 1)], 1u);
   }
   __syncthreads();
-  if (threadIdx.x < kBins) hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = cnt[threadIdx.x];
+  const int d = threadIdx.x;
+  if (d < nd) hist[by_tile ? (int64_t)blockIdx.x * nd + d : (int64_t)d * nt + blockIdx.x] = h[d];
+}
+
+// One workgroup a digit: its row of tile counts becomes the exclusive sums,
+// the digit's total goes to tot.
+__global__ void __launch_bounds__(kBlock) k_radix_rows(uint32_t *hist, int64_t nt, uint32_t *tot) {
+  uint32_t *row = hist + (int64_t)blockIdx.x * nt;
+  unsigned carry = 0u;
+  for (int64_t b = 0; b < nt; b += kTile) {
+    unsigned v[kItems], sum = 0u;
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const int64_t i = b + (int64_t)threadIdx.x * kItems + j;
+      v[j] = i < nt ? row[i] : 0u;
+      sum += v[j];
+    }
+    unsigned all;
+    unsigned ex = carry + block_exclusive_scan<unsigned>(sum, &all);
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const int64_t i = b + (int64_t)threadIdx.x * kItems + j;
+      if (i < nt) row[i] = ex;
+      ex += v[j];
+    }
+    carry += all;
+  }
+  if (threadIdx.x == 0) tot[blockIdx.x] = carry;
 }
 
 template <typename K>
 __global__ void __launch_bounds__(kBlock) k_radix_scatter(const K *kin, const int32_t *vin, K *kout, int32_t *vout,
-                                                          int64_t n, int shift, const int64_t *off,
-                                                          int64_t nblocks) {
-  __shared__ int T[kBins * kBlock];
-  const int t = threadIdx.x;
+                                                          int64_t n, int shift, int rb, const uint32_t *hist,
+                                                          const uint32_t *tot, int64_t nt, bool by_tile) {
+  __shared__ unsigned cnt[4][kBins];  // per wave: running count, then the wave's offset
+  __shared__ unsigned tex[kBins];     // the tile's exclusive offset per digit
+  __shared__ int64_t goff[kBins];     // output position of the digit's run minus tex
+  __shared__ K sk[kTile];
+  __shared__ int32_t sv[kTile];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int nd = 1 << rb;
+  const unsigned mask = (unsigned)nd - 1u;
+  const int64_t tile0 = (int64_t)blockIdx.x * kTile;
+  const int64_t wbase = tile0 + (int64_t)w * (kTile / 4);
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
-  for (int d = 0; d < kBins; ++d) T[d * kBlock + t] = 0;
-  const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)t * kItems;
-  K k[kItems];
-  int32_t v[kItems];
-  int dg[kItems];
+  for (int q = 0; q < 4; ++q) cnt[q][t] = 0u;
+  K kk[kItems];
+  int32_t vv[kItems];
+  unsigned rk[kItems];
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
-    int64_t i = base + j;
-    if (i < n) {
-      k[j] = kin[i];
-      v[j] = vin ? vin[i] : (int32_t)i;
-      dg[j] = (int)((k[j] >> shift) & (kBins - 1));
-      T[dg[j] * kBlock + t] += 1;
+    const int64_t i = std::min(wbase + (int64_t)j * 64 + lane, n - 1);  // past n: read, not used
+    kk[j] = kin[i];
+    vv[j] = vin[i];
+  }
+  // this digit's items of all tiles, and of the tiles before this one
+  unsigned mine = 0u, before = 0u;
+  if (t < nd) {
+    if (by_tile) {
+      for (int64_t q = 0; q < nt; ++q) {
+        const unsigned c = hist[q * nd + t];
+        if (q < blockIdx.x) before += c;
+        mine += c;
+      }
     } else {
-      dg[j] = -1;
+      mine = tot[t];
+      before = hist[(int64_t)t * nt + blockIdx.x];
     }
   }
   __syncthreads();
-  // exclusive scan of T in digit-major order: thread t owns entries
-  // [t*16, t*16+16)
-  int loc[kBins];
-  int s = 0;
-#pragma unroll
-  for (int q = 0; q < kBins; ++q) {
-    loc[q] = T[t * kBins + q];
-    s += loc[q];
-  }
-  int tot;
-  int ex = block_exclusive_scan<int>(s, &tot);
-#pragma unroll
-  for (int q = 0; q < kBins; ++q) {
-    int c = loc[q];
-    T[t * kBins + q] = ex;
-    ex += c;
-  }
-  __syncthreads();
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
-    if (dg[j] < 0) continue;
-    int d = dg[j];
-    int before = 0;
+    const bool valid = wbase + (int64_t)j * 64 + lane < n;
+    const unsigned d = (unsigned)(kk[j] >> shift) & mask;
+    const uint64_t peers = digit_peers(valid, d, rb);
+    const unsigned r = (unsigned)__popcll(peers & lt);
+    const unsigned c = valid ? cnt[w][d] : 0u;
+    if (valid && r == 0u) cnt[w][d] = c + (unsigned)__popcll(peers);  // the digit's first lane
+    rk[j] = valid ? ((c + r) | (d << 16)) : ~0u;
+  }
+  __syncthreads();
+  const unsigned c0 = cnt[0][t], c1 = cnt[1][t], c2 = cnt[2][t], c3 = cnt[3][t];
+  cnt[0][t] = 0u;
+  cnt[1][t] = c0;
+  cnt[2][t] = c0 + c1;
+  cnt[3][t] = c0 + c1 + c2;
+  unsigned all;
+  const unsigned ex = block_exclusive_scan<unsigned>(c0 + c1 + c2 + c3, &all);
+  const unsigned start = block_exclusive_scan<unsigned>(mine, &all);
+  tex[t] = ex;
+  goff[t] = (int64_t)start + before - ex;
+  __syncthreads();
 #pragma unroll
-    for (int q = 0; q < j; ++q) before += (dg[q] == d);
-    int64_t pos = off[(int64_t)d * nblocks + blockIdx.x] + (T[d * kBlock + t] - T[d * kBlock]) + before;
-    kout[pos] = k[j];
-    vout[pos] = v[j];
+  for (int j = 0; j < kItems; ++j)
+    if (rk[j] != ~0u) {
+      const unsigned d = rk[j] >> 16;
+      const unsigned p = tex[d] + cnt[w][d] + (rk[j] & 0xffffu);
+      sk[p] = kk[j];
+      sv[p] = vv[j];
+    }
+  __syncthreads();
+  const int m = (int)std::min<int64_t>(kTile, n - tile0);
+  for (int p = t; p < m; p += kBlock) {
+    const K k = sk[p];
+    const int64_t g = goff[(unsigned)(k >> shift) & mask] + p;
+    if (g >= 0 && g < n) {  // always true for a consistent histogram; keeps the store in bounds
+      kout[g] = k;
+      vout[g] = sv[p];
+    }
+  }
+}
+
+// At most kOneItems items, all passes in one workgroup: 16 wavefronts of 256
+// items in input order.
+template <typename K>
+__global__ void __launch_bounds__(kOneThreads) k_radix_one(K *keys, int32_t *vals, int n, int lo, int hi) {
+  constexpr int kW = kOneThreads / 64, kIt = kOneItems / kOneThreads;
+  __shared__ unsigned cnt[kW][kBins];
+  __shared__ unsigned wsum[kBins / 64];
+  __shared__ K sk[kOneItems];
+  __shared__ int32_t sv[kOneItems];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  K kk[kIt];
+  int32_t vv[kIt];
+#pragma unroll
+  for (int j = 0; j < kIt; ++j) {
+    const int i = w * 64 * kIt + j * 64 + lane;
+    kk[j] = i < n ? keys[i] : (K)0;
+    vv[j] = i < n ? vals[i] : 0;
+  }
+  for (int shift = lo; shift < hi; shift += kRadixBits) {
+    const int rb = min(kRadixBits, hi - shift);
+    const unsigned mask = (1u << rb) - 1u;
+    for (int q = t; q < kW * kBins; q += kOneThreads) (&cnt[0][0])[q] = 0u;
+    __syncthreads();
+    unsigned rk[kIt];
+#pragma unroll
+    for (int j = 0; j < kIt; ++j) {
+      const bool valid = w * 64 * kIt + j * 64 + lane < n;
+      const unsigned d = (unsigned)(kk[j] >> shift) & mask;
+      const uint64_t peers = digit_peers(valid, d, rb);
+      const unsigned r = (unsigned)__popcll(peers & lt);
+      const unsigned c = valid ? cnt[w][d] : 0u;
+      if (valid && r == 0u) cnt[w][d] = c + (unsigned)__popcll(peers);
+      rk[j] = valid ? ((c + r) | (d << 16)) : ~0u;
+    }
+    __syncthreads();
+    // per digit (threads 0-255): the waves' offsets, then the digits' starts
+    unsigned sum = 0u, x = 0u;
+    if (t < kBins) {
+#pragma unroll
+      for (int q = 0; q < kW; ++q) {
+        const unsigned c = cnt[q][t];
+        cnt[q][t] = sum;
+        sum += c;
+      }
+      x = sum;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const unsigned y = __shfl_up(x, d, 64);
+        if (lane >= d) x += y;
+      }
+      if (lane == 63) wsum[w] = x;
+    }
+    __syncthreads();
+    if (t < kBins) {
+      unsigned start = x - sum;
+      for (int q = 0; q < w; ++q) start += wsum[q];
+#pragma unroll
+      for (int q = 0; q < kW; ++q) cnt[q][t] += start;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kIt; ++j)
+      if (rk[j] != ~0u) {
+        const unsigned p = cnt[w][rk[j] >> 16] + (rk[j] & 0xffffu);
+        sk[p] = kk[j];
+        sv[p] = vv[j];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kIt; ++j) {
+      const int i = w * 64 * kIt + j * 64 + lane;
+      if (i < n) {
+        kk[j] = sk[i];
+        vv[j] = sv[i];
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kIt; ++j) {
+    const int i = w * 64 * kIt + j * 64 + lane;
+    if (i < n) {
+      keys[i] = kk[j];
+      vals[i] = vv[j];
+    }
   }
 }
 
@@ -291,21 +474,36 @@ __global__ void k_copy_pairs(const K *ks, const int32_t *vs, K *kd, int32_t *vd,
 template <typename K>
 void radix_sort_impl(Arena &ar, K *keys, int32_t *vals, int64_t n, int bits, hipStream_t s, const char *tag,
                      int lo = 0) {
-  if (n <= 1) return;
-  int64_t nb = div_up(n, kTile);
+  if (n <= 1 || bits <= lo) return;
+  if (n <= kOneItems) {
+    k_radix_one<K><<<1, kOneThreads, 0, s>>>(keys, vals, (int)n, lo, bits);
+    SPH_LAUNCH_CHECK();
+    return;
+  }
+  const int64_t nt = div_up(n, kTile);
   std::string t(tag);
   K *k2 = ar.get<K>(t + "_k2", n);
   int32_t *v2 = ar.get<int32_t>(t + "_v2", n);
-  int64_t *hist = ar.get<int64_t>(t + "_hist", (int64_t)kBins * nb + 1);
-  int64_t *off = ar.get<int64_t>(t + "_off", (int64_t)kBins * nb + 1);
+  // Where scratch is limited (a workspace cap, a fixed region) 6 bits a pass:
+  // 256 bytes of counts a tile, as the callers' stated bounds have it.
+  const Arena *own = &ar;
+  while (own->redirect) own = own->redirect;
+  const int most = own->region || (own->budget && own->budget->limit) ? 6 : kRadixBits;
+  const int passes = (bits - lo + most - 1) / most, rb0 = (bits - lo + passes - 1) / passes;
+  const bool by_tile = nt <= kSelfTiles;
+  uint32_t *hist = ar.get<uint32_t>(t + "_hist", ((int64_t)nt << rb0) + kBins);
+  uint32_t *tot = hist + ((int64_t)nt << rb0);
   K *ka = keys, *kb = k2;
   int32_t *va = vals, *vb = v2;
-  int passes = 0;
-  for (int shift = lo; shift < bits; shift += kRadixBits, ++passes) {
-    k_radix_hist<K><<<(unsigned)nb, kBlock, 0, s>>>(ka, n, shift, hist, nb);
+  for (int p = 0; p < passes; ++p) {
+    const int shift = lo + p * rb0, rb = std::min(rb0, bits - shift);
+    k_radix_hist<K><<<(unsigned)nt, kBlock, 0, s>>>(ka, n, shift, rb, hist, nt, by_tile);
     SPH_LAUNCH_CHECK();
-    scan_exclusive_i64(ar, hist, off, (int64_t)kBins * nb, false, s);
-    k_radix_scatter<K><<<(unsigned)nb, kBlock, 0, s>>>(ka, va, kb, vb, n, shift, off, nb);
+    if (!by_tile) {
+      k_radix_rows<<<1u << rb, kBlock, 0, s>>>(hist, nt, tot);
+      SPH_LAUNCH_CHECK();
+    }
+    k_radix_scatter<K><<<(unsigned)nt, kBlock, 0, s>>>(ka, va, kb, vb, n, shift, rb, hist, tot, nt, by_tile);
     SPH_LAUNCH_CHECK();
     std::swap(ka, kb);
     std::swap(va, vb);
@@ -350,7 +548,7 @@ __device__ inline int64_t xcd_tile(int64_t ntiles) {
 // count nothing and write nothing).
 template <int NB, int IT>
 __global__ void __launch_bounds__(kSortThreads) k_kv_hist(const uint32_t *key, int64_t n, const int64_t *dn,
-                                                         int shift, int rb, int64_t ntiles, int64_t *hist) {
+                                                         int shift, int rb, int64_t ntiles, uint32_t *hist) {
   constexpr int kTileN = kSortThreads * IT;  // items per tile
   __shared__ unsigned h[NB];
   if (dn) n = *dn;
@@ -373,7 +571,8 @@ __global__ void __launch_bounds__(kSortThreads) k_kv_hist(const uint32_t *key, i
 template <int NB, int IT>
 __global__ void __launch_bounds__(kSortThreads) k_kv_scatter(const uint32_t *kin, const int32_t *ain,
                                                             const double *bin, int64_t n, const int64_t *dn,
-                                                            int shift, int rb, int64_t ntiles, const int64_t *off,
+                                                            int shift, int rb, int64_t ntiles,
+                                                            const uint32_t *hist, const uint32_t *dtot,
                                                             uint32_t *kout, int32_t *aout, double *bout) {
   constexpr int kTileN = kSortThreads * IT;  // items per tile
   constexpr int kPer = NB / kSortThreads > 0 ? NB / kSortThreads : 1;  // digits per thread
@@ -444,13 +643,23 @@ __global__ void __launch_bounds__(kSortThreads) k_kv_scatter(const uint32_t *kin
   }
   unsigned tot;
   unsigned ex = block_exclusive_scan<unsigned>(sum, &tot);
+  // the digits' starts in the output, from their totals over all tiles
+  unsigned gt[kPer], gsum = 0u;
+#pragma unroll
+  for (int m = 0; m < kPer; ++m) {
+    const int d = t * kPer + m;
+    gt[m] = d < nd ? dtot[d] : 0u;
+    gsum += gt[m];
+  }
+  unsigned gex = block_exclusive_scan<unsigned>(gsum, &tot);
 #pragma unroll
   for (int m = 0; m < kPer; ++m) {
     const int d = t * kPer + m;
     if (d < nd) {
       tex[d] = ex;
-      goff[d] = off[(int64_t)d * ntiles + tile] - (int64_t)ex;
+      goff[d] = (int64_t)gex + hist[(int64_t)d * ntiles + tile] - (int64_t)ex;
       ex += loc[m];
+      gex += gt[m];
     }
   }
   __syncthreads();
@@ -483,13 +692,14 @@ void kv_pass(Arena &ar, int64_t n, const int64_t *dn, int shift, int rb, const u
   constexpr int kTileN = kSortThreads * IT;
   const int64_t ntiles = div_up(n, kTileN);
   const int64_t m = ((int64_t)1 << rb) * ntiles;
-  int64_t *hist = ar.get<int64_t>("kv_hist", m + 1);
-  int64_t *off = ar.get<int64_t>("kv_off", m + 1);
+  uint32_t *hist = ar.get<uint32_t>("kv_hist", m + NB);
+  uint32_t *tot = hist + m;
   k_kv_hist<NB, IT><<<(unsigned)ntiles, kSortThreads, 0, s>>>(kin, n, dn, shift, rb, ntiles, hist);
   SPH_LAUNCH_CHECK();
-  scan_exclusive_i64(ar, hist, off, m, false, s);
-  k_kv_scatter<NB, IT><<<(unsigned)ntiles, kSortThreads, 0, s>>>(kin, ain, bin, n, dn, shift, rb, ntiles, off, kout,
-                                                              aout, bout);
+  k_radix_rows<<<1u << rb, kBlock, 0, s>>>(hist, ntiles, tot);
+  SPH_LAUNCH_CHECK();
+  k_kv_scatter<NB, IT><<<(unsigned)ntiles, kSortThreads, 0, s>>>(kin, ain, bin, n, dn, shift, rb, ntiles, hist, tot,
+                                                              kout, aout, bout);
   SPH_LAUNCH_CHECK();
 }
 
