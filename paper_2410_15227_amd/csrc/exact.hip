@@ -443,6 +443,7 @@ struct ExactInst {
   const int64_t *gbase;
   long long *gift;
   uint8_t *wflag;  // bit 0: S (inside); bit 1: left to the redo kernel
+  int64_t C;       // cells
 };
 constexpr uint8_t kFlagInside = 1, kFlagRedo = 2;
 
@@ -1185,52 +1186,70 @@ __global__ void k_gift_check(ExactInst *inst, const int64_t *total, int64_t cap,
 
 // w = S - (own + received) / (4 pi) for every pair the edge kernel kept:
 // its own total waits in w as a 64-bit integer until here.  One wavefront
-// per cell takes its pairs kGatherW at a time (their particles in LDS).  The
-// faces of the cell that a twin evaluates are listed first, with the twin's
-// list and the face's gift run (both contiguous); their rows are then read
-// kGatherU blocks of 64 at a time (loads in flight together), and each gift
-// goes, with the opposite sign, to the pair of this cell with the same
-// particle (bisection in LDS).  Integer sums: the order does not matter.
+// per cell takes its pairs kGatherW at a time, their particles in a hash table
+// in LDS.  The faces of the cell that a twin evaluates are listed first, with
+// the twin's list and the face's gift run (both contiguous); the rows of all
+// of them are then read as one run, kGatherU blocks of 64 at a time (loads in
+// flight together), and each gift goes, with the opposite sign, to the pair of
+// this cell with the same particle.  Integer sums: the order does not matter.
+// A workgroup is one wavefront and one cell, handed out as others end (cells
+// differ in their pairs, and so do eighths of the cells: one to each XCD took
+// 2.53 ms where this order took 1.76), and blockIdx.y is the instance, so that
+// the small ones of a batch run side by side.  2.7 GB are read for the 34M
+// pairs of a 262,144-particle cloud; bounded by the latency of its loads at 28
+// wavefronts a CU.  In ms, before (bisection in LDS, blocks face by face,
+// persistent wavefronts, a launch an instance) and now (MI355X): those pairs
+// 1.52 and 1.04, 512 particles 0.061 and 0.027, eight clouds 1.41 and 0.63.
 constexpr int kGatherW = 256;
-constexpr int kGatherWaves = 4;
 constexpr int kGatherU = 4;
-__global__ void __launch_bounds__(64 * kGatherWaves) k_exact_gather(const ExactInst *__restrict__ insts, int ins,
-                                                                    int64_t C) {
-  __shared__ int32_t pl_[kGatherWaves][kGatherW];
-  __shared__ unsigned long long ga_[kGatherWaves][kGatherW];
-  __shared__ int64_t fcb_[kGatherWaves][64], fgs_[kGatherWaves][64];
-  __shared__ int32_t fra_[kGatherWaves][64], frb_[kGatherWaves][64];
-  const ExactInst &I = insts[ins];
+constexpr int kGatherF = 32;               // faces at a time
+constexpr int kGatherHash = 2 * kGatherW;  // open addressing: half of it at most is taken
+struct GatherWave {
+  int32_t key[kGatherHash];  // particle, -1: free
+  uint8_t at[kGatherHash];   // its pair in the window
+  unsigned long long ga[kGatherW];
+  // per face taken from a twin: the end of its rows among all of them, and
+  // what leads from a row's number to its pair and to its gift
+  int64_t end[kGatherF], to_pair[kGatherF], to_gift[kGatherF];
+};
+__device__ __forceinline__ uint32_t gather_slot(int32_t i) { return ((uint32_t)i * 2654435769u) >> 23; }
+static_assert(kGatherHash == 1 << 9 && kGatherW <= 256, "gather_slot and at");
+
+__global__ void __launch_bounds__(64) k_exact_gather(const ExactInst *__restrict__ insts) {
+  __shared__ GatherWave L;
+  const ExactInst &I = insts[blockIdx.y];
   if (!I.gift) return;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int32_t *const pl = pl_[wid];
-  unsigned long long *const ga = ga_[wid];
-  int64_t *const fcb = fcb_[wid], *const fgs = fgs_[wid];
-  int32_t *const fra = fra_[wid], *const frb = frb_[wid];
+  const int lane = threadIdx.x;
   const int64_t *coff = I.cell_off;
   const int32_t *pair_p = I.pair_p;
-  for (int64_t cp = (int64_t)blockIdx.x * kGatherWaves + wid; cp < C; cp += (int64_t)gridDim.x * kGatherWaves) {
+  for (int64_t cp = blockIdx.x; cp < I.C; cp += gridDim.x) {
     const int64_t b = coff[cp], n = coff[cp + 1] - b;
     const int64_t f0 = I.cfo[cp], nf = I.cfo[cp + 1] - f0;
     for (int64_t w0 = 0; w0 < n; w0 += kGatherW) {
       const int m = (int)min((int64_t)kGatherW, n - w0);
+      for (int l = lane; l < kGatherHash; l += 64) L.key[l] = -1;
+      wave_sync();
       for (int l = lane; l < m; l += 64) {
-        pl[l] = pair_p[b + w0 + l];
-        ga[l] = 0ull;
+        const int32_t i = pair_p[b + w0 + l];
+        L.ga[l] = 0ull;
+        uint32_t q = gather_slot(i);
+        while (atomicCAS(&L.key[q], -1, i) != -1) q = (q + 1) & (kGatherHash - 1);  // a cell lists a particle once
+        L.at[q] = (uint8_t)l;
       }
       wave_sync();
-      const int32_t i_lo = pl[0], i_hi = pl[m - 1];
-      for (int64_t fw = 0; fw < nf; fw += 64) {
+      // the window's first and last particle (its list ascends)
+      const int32_t i_lo = pair_p[b + w0], i_hi = pair_p[b + w0 + m - 1];
+      for (int64_t fw = 0; fw < nf; fw += kGatherF) {
         const int64_t f = f0 + fw + lane;
-        const int code = fw + lane < nf ? I.fcode[f] : 0;
+        const int code = lane < kGatherF && fw + lane < nf ? I.fcode[f] : 0;
         const bool inc = code <= -2;
         const uint64_t mk = __ballot(inc);
+        const int nin = __popcll(mk);
+        if (nin == 0) continue;
+        int64_t to_pair = 0, to_gift = 0, rows = 0;
         if (inc) {
-          const int pos = mbcnt64(mk);
           const int64_t tc = I.ftwin[f];
           const int64_t cb = coff[tc], nc = coff[tc + 1] - cb;
-          fcb[pos] = cb;
-          fgs[pos] = I.gbase[tc] + (int64_t)(-2 - code) * nc;
           // the twin's rows whose particles fall in this window's range
           // [i_lo, i_hi] (its list ascends by particle): all of them when the
           // cell takes one or two windows, else found by bisection, so that a
@@ -1252,49 +1271,59 @@ __global__ void __launch_bounds__(64 * kGatherWaves) k_exact_gather(const ExactI
             }
             rb = lo;
           }
-          fra[pos] = ra;
-          frb[pos] = rb;
+          rows = rb - ra;
+          to_pair = cb + ra;
+          to_gift = I.gbase[tc] + (int64_t)(-2 - code) * nc + ra;
         }
-        const int nin = __popcll(mk);
-        wave_sync();
-        int j = 0, r = 0;  // next block: rows fra[j] + [64 r, 64 r + 64) of face j's run
-        while (j < nin) {
-          int64_t gs[kGatherU], cb[kGatherU];
-          bool uv[kGatherU];
+        int64_t end = rows;
 #pragma unroll
-          for (int u = 0; u < kGatherU; ++u) {
-            const int jj = min(j, nin - 1);
-            const int64_t t = fra[jj] + 64 * (int64_t)r + lane;
-            uv[u] = j < nin && t < frb[jj];
-            gs[u] = j < nin ? fgs[j] + t : 0;
-            cb[u] = j < nin ? fcb[j] + t : 0;
-            if (j < nin) {
-              if (fra[j] + 64 * (r + 1) < frb[j]) {
-                ++r;
-              } else {
-                ++j;
-                r = 0;
-              }
-            }
-          }
+        for (int d = 1; d < kGatherF; d <<= 1) {
+          const int64_t y = __shfl_up(end, d, 64);
+          if (lane >= d) end += y;
+        }
+        if (inc) {
+          const int pos = mbcnt64(mk);
+          L.end[pos] = end;
+          L.to_pair[pos] = to_pair - (end - rows);
+          L.to_gift[pos] = to_gift - (end - rows);
+        }
+        wave_sync();
+        const int64_t total = L.end[nin - 1];
+        int j = 0;  // the face of this lane's row
+        int64_t je = L.end[0], jp = L.to_pair[0], jg = L.to_gift[0];
+        for (int64_t x0 = 0; x0 < total; x0 += 64 * kGatherU) {
           long long T[kGatherU];
           int32_t ip[kGatherU];
 #pragma unroll
           for (int u = 0; u < kGatherU; ++u) {
-            T[u] = uv[u] ? I.gift[gs[u]] : 0;
-            ip[u] = uv[u] ? pair_p[cb[u]] : 0;
+            const int64_t x = x0 + 64 * u + lane;
+            T[u] = 0;
+            ip[u] = 0;
+            if (x < total) {
+              while (x >= je) {
+                ++j;
+                je = L.end[j];
+                jp = L.to_pair[j];
+                jg = L.to_gift[j];
+              }
+              T[u] = I.gift[jg + x];
+              ip[u] = pair_p[jp + x];
+            }
+          }
+          uint32_t q[kGatherU];
+          int32_t key[kGatherU];
+#pragma unroll
+          for (int u = 0; u < kGatherU; ++u) {
+            q[u] = gather_slot(ip[u]);
+            key[u] = T[u] != 0 ? L.key[q[u]] : -1;
           }
 #pragma unroll
           for (int u = 0; u < kGatherU; ++u) {
-            if (T[u] != 0 && ip[u] >= i_lo && ip[u] <= i_hi) {
-              int lo = 0, hi = m;
-              while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (pl[mid] < ip[u]) lo = mid + 1;
-                else hi = mid;
-              }
-              if (lo < m && pl[lo] == ip[u]) atomicAdd(&ga[lo], (unsigned long long)(-T[u]));
+            while (key[u] != -1 && key[u] != ip[u]) {
+              q[u] = (q[u] + 1) & (kGatherHash - 1);
+              key[u] = L.key[q[u]];
             }
+            if (key[u] != -1) atomicAdd(&L.ga[L.at[q[u]]], (unsigned long long)(-T[u]));
           }
         }
         wave_sync();
@@ -1303,7 +1332,7 @@ __global__ void __launch_bounds__(64 * kGatherWaves) k_exact_gather(const ExactI
         const int64_t jj = b + w0 + l;
         const uint8_t fl = I.wflag[jj];
         if (!(fl & kFlagRedo)) {
-          const unsigned long long tot = (unsigned long long)__double_as_longlong(I.w[jj]) + ga[l];
+          const unsigned long long tot = (unsigned long long)__double_as_longlong(I.w[jj]) + L.ga[l];
           I.w[jj] = ((fl & kFlagInside) ? 1.0 : 0.0) - kInv4Pi * from_fixed(tot);
         }
       }
@@ -2139,17 +2168,19 @@ static ExactInst inst_of_job(const ExactJob &j, const GiftPlan *G, int k) {
                    t.fsphere, t.fplane32, t.fvpos32, t.edgeA, t.edgeE, t.edgeM, t.fvpos, P.w, P.n_pairs,
                    P.cell_off, sh ? t.face_code : nullptr, sh ? t.cell_slots : nullptr, sh ? t.face_twin : nullptr,
                    sh ? G->gbase + G->gb_off[k] : nullptr, sh ? G->gift + G->gift_off[k] : nullptr,
-                   sh ? G->wflag + G->flag_off[k] : nullptr};
+                   sh ? G->wflag + G->flag_off[k] : nullptr, t.n_cells};
 }
 
 // the gather pass of every instance with gifts (device table d_inst)
-static void launch_gather(Ctx &ctx, const std::vector<ExactJob> &jobs, const GiftPlan &G, const ExactInst *d_inst,
+static void launch_gather(const std::vector<ExactJob> &jobs, const GiftPlan &G, const ExactInst *d_inst,
                           hipStream_t s) {
-  for (int k = 0; k < (int)jobs.size(); ++k) {
-    if (G.gb_off[k] < 0) continue;
-    const int64_t C = jobs[k].t->n_cells;
-    const int64_t blocks = std::min<int64_t>(div_up(C, kGatherWaves), (int64_t)ctx.n_cu * 8);
-    k_exact_gather<<<(unsigned)blocks, 64 * kGatherWaves, 0, s>>>(d_inst, k, C);
+  if (!G.any) return;
+  int64_t C = 0;
+  for (size_t k = 0; k < jobs.size(); ++k)
+    if (G.gb_off[k] >= 0) C = std::max(C, jobs[k].t->n_cells);
+  for (size_t k = 0; k < jobs.size(); k += 32768) {  // below the limit of a grid's y
+    const unsigned ny = (unsigned)std::min<size_t>(jobs.size() - k, 32768);
+    k_exact_gather<<<dim3((unsigned)std::min<int64_t>(C, 1 << 24), ny), 64, 0, s>>>(d_inst + k);
     SPH_LAUNCH_CHECK();
   }
 }
@@ -2232,7 +2263,7 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
     k_exact_mixed_list<<<(unsigned)(ctx.n_cu * 4), 256, 0, s>>>(redo, next + kRedoCtr, d_inst, tab->chunk0, n_inst,
                                                                 nullptr);
     SPH_LAUNCH_CHECK();
-    launch_gather(ctx, jobs, G, d_inst, s);
+    launch_gather(jobs, G, d_inst, s);
     return;
   }
   int64_t *ctr = ctx.counting ? ctx.d_counters : nullptr;
@@ -2338,7 +2369,7 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   kr.done();
   if (shared) {
     KernelTimer kg(&ctx, "exact_gather", s);
-    launch_gather(ctx, jobs, G, d_inst, s);
+    launch_gather(jobs, G, d_inst, s);
     kg.done();
   }
 }
