@@ -32,6 +32,8 @@
 namespace sphmap {
 namespace {
 
+constexpr int kKdLevels = 66;  // depths to 62, their children's end, and one more
+
 struct KdNodes {
   uint64_t *label;
   int32_t *level, *parent, *first, *count, *left, *nleft;
@@ -45,20 +47,34 @@ struct KdNodes {
 
 __global__ void k_kd_check(int64_t n, const double *xyz, const double *m, int *bad, unsigned long long *mmax) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  for (int k = 0; k < 3; ++k) {
-    const double x = xyz[3 * i + k];
-    if (!(x >= 0.0 && x < 1.0)) atomicOr(bad, 1);
+  unsigned long long most = 0ull;
+  if (i < n) {
+    for (int k = 0; k < 3; ++k) {
+      const double x = xyz[3 * i + k];
+      if (!(x >= 0.0 && x < 1.0)) atomicOr(bad, 1);
+    }
+    const double mi = m[i];
+    if (!(mi > 0.0 && mi < INFINITY)) atomicOr(bad, 2);
+    else most = (unsigned long long)__double_as_longlong(mi);
   }
-  const double mi = m[i];
-  if (!(mi > 0.0 && mi < INFINITY)) atomicOr(bad, 2);
-  else atomicMax(mmax, (unsigned long long)__double_as_longlong(mi));
+  // one maximum a wavefront: n of them on one address took 53 us for 262,139
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long u = __shfl_xor(most, o, 64);
+    if (u > most) most = u;
+  }
+  if ((threadIdx.x & 63) == 0 && most) atomicMax(mmax, most);
+}
+
+__device__ inline void kd_zero(KdNodes N, int64_t k) {  // before the node's sums
+  N.q[4 * k] = N.q[4 * k + 1] = N.q[4 * k + 2] = N.q[4 * k + 3] = 0;
+  N.s2[k] = 0ull;
 }
 
 // pxm[i] holds the position and mass of particle perm[i], so that the
 // per-level kernels read their particles contiguously instead of gathering
 __global__ void k_kd_init(int64_t n, const double *xyz, const double *m, int32_t *perm, int32_t *nop,
-                          double4 *pxm, KdNodes N) {
+                          double4 *pxm, KdNodes N, int64_t *lv) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
     perm[i] = (int32_t)i;
@@ -74,14 +90,10 @@ __global__ void k_kd_init(int64_t n, const double *xyz, const double *m, int32_t
     N.left[0] = -1;
     N.lo[0] = make_double4(0.0, 0.0, 0.0, 0.0);
     N.hi[0] = make_double4(1.0, 1.0, 1.0, 0.0);
+    kd_zero(N, 0);
+    lv[0] = 0;
+    lv[1] = 1;
   }
-}
-
-__global__ void k_kd_zero(int64_t b, int64_t e, KdNodes N) {
-  const int64_t k = b + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= e) return;
-  N.q[4 * k] = N.q[4 * k + 1] = N.q[4 * k + 2] = N.q[4 * k + 3] = 0;
-  N.s2[k] = 0ull;
 }
 
 // Levels with at most kLdsNodes nodes (the top of the tree, where every
@@ -126,9 +138,10 @@ struct WaveRuns {
   }
 };
 
-__global__ void __launch_bounds__(256) k_kd_sums(int64_t n, const double4 *pxm, const int32_t *nop, int64_t b,
-                                                 int64_t e, int K, KdNodes N) {
+__global__ void __launch_bounds__(256) k_kd_sums(int64_t n, const double4 *pxm, const int32_t *nop, const int64_t *lv,
+                                                 int K, KdNodes N) {
 #pragma clang fp contract(off)
+  const int64_t b = lv[0], e = lv[1];
   __shared__ unsigned long long acc[4 * kLdsNodes];
   const bool lds = e - b <= kLdsNodes;
   if (lds) {
@@ -168,7 +181,8 @@ __global__ void __launch_bounds__(256) k_kd_sums(int64_t n, const double4 *pxm, 
   }
 }
 
-__global__ void k_kd_com(int64_t b, int64_t e, int K, int leaf_split, int max_depth, KdNodes N) {
+__global__ void k_kd_com(const int64_t *lv, int K, int leaf_split, int max_depth, KdNodes N) {
+  const int64_t b = lv[0], e = lv[1];
   const int64_t k = b + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= e) return;
   const double qm = (double)N.q[4 * k];
@@ -196,8 +210,9 @@ __global__ void k_kd_com(int64_t b, int64_t e, int K, int leaf_split, int max_de
 }
 
 __global__ void __launch_bounds__(256) k_kd_size_flags(int64_t n, const double4 *pxm, const int32_t *nop,
-                                                       int64_t b, int64_t e, KdNodes N, int64_t *flag) {
+                                                       const int64_t *lv, KdNodes N, int64_t *flag) {
 #pragma clang fp contract(off)
+  const int64_t b = lv[0], e = lv[1];
   __shared__ unsigned long long mx[kLdsNodes];
   const bool lds = e - b <= kLdsNodes;
   if (lds) {
@@ -237,25 +252,19 @@ __global__ void __launch_bounds__(256) k_kd_size_flags(int64_t n, const double4 
   }
 }
 
-// children per splitting node: 2 when both sides are non-empty
-__global__ void k_kd_nch(int64_t b, int64_t e, const int64_t *scan, KdNodes N, int64_t *nch) {
-  const int64_t k = b + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= e) return;
-  int64_t c = 0;
-  if (N.axis[k] >= 0) {
-    const int64_t f = N.first[k], cnt = N.count[k];
-    const int64_t nl = scan[f + cnt] - scan[f];
-    N.nleft[k] = (int32_t)nl;
-    if (nl > 0 && nl < cnt) c = 2;
-    else N.axis[k] = -1;
-  }
-  nch[k - b] = c;
+// children of node k: 2 when it splits and both sides are non-empty
+__device__ inline int kd_nch(int64_t k, const int64_t *scan, KdNodes N) {
+  if (N.axis[k] < 0) return 0;
+  const int64_t f = N.first[k], cnt = N.count[k];
+  const int64_t nl = scan[f + cnt] - scan[f];
+  N.nleft[k] = (int32_t)nl;
+  if (nl > 0 && nl < cnt) return 2;
+  N.axis[k] = -1;
+  return 0;
 }
 
-__global__ void k_kd_children(int64_t b, int64_t e, int64_t base, const int64_t *choff, KdNodes N) {
-  const int64_t k = b + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= e || N.axis[k] < 0) return;
-  const int64_t l = base + choff[k - b];
+// the children l and l + 1 of splitting node k
+__device__ inline void kd_children(int64_t k, int64_t l, KdNodes N) {
   const int a = N.axis[k];
   const double sp = N.split[k];
   N.left[k] = (int32_t)l;
@@ -279,12 +288,48 @@ __global__ void k_kd_children(int64_t b, int64_t e, int64_t base, const int64_t 
     }
     N.lo[c] = lo;
     N.hi[c] = hi;
+    kd_zero(N, c);
   }
 }
 
+// A level of at most kKdOne nodes in one workgroup: children counted, numbered
+// and written, and the next level's range.
+constexpr int kKdOne = 1024;
+__global__ void __launch_bounds__(kKdOne) k_kd_split(int64_t *lv, const int64_t *scan, KdNodes N) {
+  __shared__ int wsum[kKdOne / 64];
+  const int64_t b = lv[0], e = lv[1];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int64_t k = b + tid;
+  const bool splits = k < e && kd_nch(k, scan, N) > 0;
+  const uint64_t m = __ballot(splits);
+  if (lane == 0) wsum[wid] = __popcll(m);
+  __syncthreads();
+  int before = 0, all = 0;
+  for (int w = 0; w < kKdOne / 64; ++w) {
+    if (w < wid) before += wsum[w];
+    all += wsum[w];
+  }
+  if (splits) kd_children(k, e + 2 * (int64_t)(before + __popcll(m & (lane == 0 ? 0ull : ~0ull >> (64 - lane)))), N);
+  if (tid == 0) lv[2] = e + 2 * (int64_t)all;
+}
+
+// Longer levels, of up to nb nodes, in three steps: counts, their scan, children.
+__global__ void k_kd_nch(const int64_t *lv, int64_t nb, const int64_t *scan, KdNodes N, int64_t *nch) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < nb) nch[t] = lv[0] + t < lv[1] ? kd_nch(lv[0] + t, scan, N) : 0;
+}
+
+__global__ void k_kd_children(int64_t *lv, int64_t nb, const int64_t *choff, KdNodes N) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k = lv[0] + t, e = lv[1];
+  if (t == 0) lv[2] = e + choff[nb];
+  if (t < nb && k < e && N.axis[k] >= 0) kd_children(k, e + choff[t], N);
+}
+
 __global__ void k_kd_permute(int64_t n, const int32_t *perm, const int32_t *nop, const double4 *pxm, int32_t *perm2,
-                             int32_t *nop2, double4 *pxm2, int64_t b, int64_t e, const int64_t *scan,
+                             int32_t *nop2, double4 *pxm2, const int64_t *lv, const int64_t *scan,
                              const int64_t *flag, KdNodes N) {
+  const int64_t b = lv[0], e = lv[1];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int64_t node = nop[i];
@@ -535,40 +580,66 @@ void kd_pseudo_build(Ctx &ctx, KdArgs &ka, hipStream_t s) {
   int32_t *nop = ar.get<int32_t>("kd_nop", n), *nop2 = ar.get<int32_t>("kd_nop2", n);
   double4 *pxm = ar.get<double4>("kd_pxm", n), *pxm2 = ar.get<double4>("kd_pxm2", n);
   int64_t *flag = ar.get<int64_t>("kd_flag", n + 1), *scan = ar.get<int64_t>("kd_scan", n + 1);
-  k_kd_init<<<grid_of(n), 256, 0, s>>>(n, a.xyz, a.m, perm, nop, pxm, N);
+  // the levels' first nodes (in a buffer that is filled after the build)
+  int64_t *lv = (int64_t *)ar.get<int32_t>("kd_unit_at", std::max<int64_t>(n, 2 * kKdLevels));
+  k_kd_init<<<grid_of(n), 256, 0, s>>>(n, a.xyz, a.m, perm, nop, pxm, N, lv);
   SPH_LAUNCH_CHECK();
+  // The levels' sizes stay on the device: a run of levels is launched on an
+  // upper bound of its nodes (twice as many a level), and read back at its
+  // end.  The first run is as deep as the tree has to be for leaves of fewer
+  // than leaf_split particles, the others two levels; a level past the last is
+  // empty and changes nothing.  A run of one level, as under a workspace cap,
+  // knows its exact size, and takes no more scratch than that.
+  // With every level's size waited for (45 us) and 13 launches a level where
+  // there are 7 to 10 now, builds of 262,139 and 8,000 particles took 2.69 and
+  // 1.64 ms; they take 2.12 and 1.15 (MI355X).
   std::vector<int64_t> loff = {0, 1};
   {
     KernelTimer kt(&ctx, "kd_build", s);
+    int run = 1;
+    if (!ctx.ws.limit)
+      while (((int64_t)ka.leaf_split << run) <= n) ++run;
     for (;;) {
-      const int64_t b = loff[loff.size() - 2], e = loff.back();
-      const int64_t cnt = e - b;
-      k_kd_zero<<<grid_of(cnt), 256, 0, s>>>(b, e, N);
-      SPH_LAUNCH_CHECK();
-      k_kd_sums<<<grid_of(n), 256, 0, s>>>(n, pxm, nop, b, e, K, N);
-      SPH_LAUNCH_CHECK();
-      k_kd_com<<<grid_of(cnt), 256, 0, s>>>(b, e, K, ka.leaf_split, o.max_depth, N);
-      SPH_LAUNCH_CHECK();
-      k_kd_size_flags<<<grid_of(n), 256, 0, s>>>(n, pxm, nop, b, e, N, flag);
-      SPH_LAUNCH_CHECK();
-      scan_exclusive_i64(ar, flag, scan, n, true, s);
-      int64_t *nch = ar.get<int64_t>("kd_nch", cnt + 1), *choff = ar.get<int64_t>("kd_choff", cnt + 1);
-      k_kd_nch<<<grid_of(cnt), 256, 0, s>>>(b, e, scan, N, nch);
-      SPH_LAUNCH_CHECK();
-      scan_exclusive_i64(ar, nch, choff, cnt, true, s);
-      int64_t tot = 0;
-      SPH_HIP(hipMemcpyAsync(&tot, choff + cnt, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+      const int d0 = (int)loff.size() - 2;
+      const int d1 = std::min(d0 + run, o.max_depth + 1);
+      int64_t nb = loff[d0 + 1] - loff[d0];
+      for (int d = d0; d < d1; ++d, nb = std::min(2 * nb, n)) {
+        int64_t *l = lv + d;
+        k_kd_sums<<<grid_of(n), 256, 0, s>>>(n, pxm, nop, l, K, N);
+        SPH_LAUNCH_CHECK();
+        k_kd_com<<<grid_of(nb), 256, 0, s>>>(l, K, ka.leaf_split, o.max_depth, N);
+        SPH_LAUNCH_CHECK();
+        k_kd_size_flags<<<grid_of(n), 256, 0, s>>>(n, pxm, nop, l, N, flag);
+        SPH_LAUNCH_CHECK();
+        scan_exclusive_i64(ar, flag, scan, n, true, s);
+        const int64_t room = ctx.ws.limit ? nb : n;  // no growth between the launches of a run
+        int64_t *nch = ar.get<int64_t>("kd_nch", room + 1), *choff = ar.get<int64_t>("kd_choff", room + 1);
+        if (nb <= kKdOne) {
+          k_kd_split<<<1, kKdOne, 0, s>>>(l, scan, N);
+          SPH_LAUNCH_CHECK();
+        } else {
+          k_kd_nch<<<grid_of(nb), 256, 0, s>>>(l, nb, scan, N, nch);
+          SPH_LAUNCH_CHECK();
+          scan_exclusive_i64(ar, nch, choff, nb, true, s);
+          k_kd_children<<<grid_of(nb), 256, 0, s>>>(l, nb, choff, N);
+          SPH_LAUNCH_CHECK();
+        }
+        k_kd_permute<<<grid_of(n), 256, 0, s>>>(n, perm, nop, pxm, perm2, nop2, pxm2, l, scan, flag, N);
+        SPH_LAUNCH_CHECK();
+        std::swap(perm, perm2);
+        std::swap(nop, nop2);
+        std::swap(pxm, pxm2);
+      }
+      int64_t got[kKdLevels];
+      SPH_HIP(hipMemcpyAsync(got, lv + d0 + 2, (d1 - d0) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
       SPH_HIP(hipStreamSynchronize(s));
-      if (tot == 0) break;
-      SPH_REQUIRE(e + tot <= cap, SPHMAP_EINVAL, "k-d tree larger than 2n nodes");
-      k_kd_children<<<grid_of(cnt), 256, 0, s>>>(b, e, e, choff, N);
-      SPH_LAUNCH_CHECK();
-      k_kd_permute<<<grid_of(n), 256, 0, s>>>(n, perm, nop, pxm, perm2, nop2, pxm2, b, e, scan, flag, N);
-      SPH_LAUNCH_CHECK();
-      std::swap(perm, perm2);
-      std::swap(nop, nop2);
-      std::swap(pxm, pxm2);
-      loff.push_back(e + tot);
+      bool done = false;
+      for (int d = d0; d < d1 && !done; ++d) {
+        done = got[d - d0] == loff.back();
+        if (!done) loff.push_back(got[d - d0]);
+      }
+      if (done) break;
+      run = ctx.ws.limit ? 1 : 2;
     }
     kt.done();
   }
@@ -588,7 +659,7 @@ void kd_pseudo_build(Ctx &ctx, KdArgs &ka, hipStream_t s) {
   int8_t *acc = ar.get<int8_t>("kd_acc", nn);
   k_kd_accept<<<grid_of(nn), 256, 0, s>>>(nn, N, a.n_src, src, o.r_part, ka.r_leaf, o.theta, a.n_open, op, acc);
   SPH_LAUNCH_CHECK();
-  int32_t *unit_at = ar.get<int32_t>("kd_unit_at", n);
+  int32_t *unit_at = (int32_t *)lv;
   k_kd_fill<<<grid_of(n), 256, 0, s>>>(unit_at, -1, n);
   SPH_LAUNCH_CHECK();
   k_kd_units<<<grid_of(nn), 256, 0, s>>>(nn, N, acc, unit_at);
