@@ -12,6 +12,7 @@ struct sphmap_ctx {
 };
 struct sphmap_tess {
   sphmap::TessDev t;
+  sphmap_ctx *maker = nullptr;  // the context whose pool its blocks go back to
 };
 struct sphmap_pairs {
   sphmap::PairsDev p;
@@ -53,11 +54,28 @@ sphmap_pairs *new_pairs(sphmap::Ctx &C) {
   return q;
 }
 
+// A grid allocates from the pool of the context that makes it, unless that
+// context's workspace is capped, and gives its blocks back when that context
+// frees it; between the two any context may use it, so it holds no pool.
+std::unique_ptr<sphmap_tess> new_tess(sphmap_ctx *ctx) {
+  std::unique_ptr<sphmap_tess> T(new sphmap_tess);
+  if (!ctx->c.ws.limit) {
+    T->t.mem.pool = &ctx->c.pool;
+    T->maker = ctx;
+  }
+  return T;
+}
+sphmap_tess *made_tess(std::unique_ptr<sphmap_tess> &T) {
+  T->t.mem.pool = nullptr;
+  return T.release();
+}
+
 // The context's pair list for calls that keep none (counted in its workspace).
 sphmap::PairsDev *scratch_pairs(sphmap::Ctx &C) {
   if (!C.scratch_pairs) {
     C.scratch_pairs = new sphmap::PairsDev;
     C.scratch_pairs->mem.budget = &C.ws;
+    C.scratch_pairs->mem.spare = &C.pool;
   }
   return C.scratch_pairs;
 }
@@ -121,6 +139,7 @@ int sphmap_create(int32_t device, size_t workspace_bytes, sphmap_ctx **out) {
   ctx->c.device = device;
   ctx->c.ws.limit = workspace_bytes;
   ctx->c.arena.budget = &ctx->c.ws;
+  ctx->c.arena.spare = &ctx->c.pool;
   int rc = guarded(ctx.get(), [&] {
     size_t free_b = 0, total_b = 0;
     SPH_HIP(hipMemGetInfo(&free_b, &total_b));
@@ -169,7 +188,7 @@ int sphmap_tess_upload(sphmap_ctx *ctx, int64_t n_cells, int64_t n_faces, int64_
                        const int64_t *h_face_vtx_off, const int32_t *h_face_vtx, void *stream, sphmap_tess **out) {
   if (!ctx || !out) return SPHMAP_EINVAL;
   *out = nullptr;
-  std::unique_ptr<sphmap_tess> T(new sphmap_tess);
+  std::unique_ptr<sphmap_tess> T = new_tess(ctx);
   int rc = guarded(ctx, [&] {
     SPH_REQUIRE(n_cells >= 1 && n_cells < ((int64_t)1 << 31), SPHMAP_EINVAL, "n_cells out of range");
     SPH_REQUIRE(n_faces >= 0 && n_faces < ((int64_t)1 << 31), SPHMAP_EINVAL, "n_faces out of range");
@@ -226,7 +245,7 @@ int sphmap_tess_upload(sphmap_ctx *ctx, int64_t n_cells, int64_t n_faces, int64_
     sphmap::tess_prepare(ctx->c, t, s);
   });
   if (rc != SPHMAP_OK) return rc;
-  *out = T.release();
+  *out = made_tess(T);
   return SPHMAP_OK;
 }
 
@@ -257,7 +276,7 @@ int sphmap_tess_build_voronoi(sphmap_ctx *ctx, int64_t n, const double *d_genera
                               sphmap_tess **out) {
   if (!ctx || !out) return SPHMAP_EINVAL;
   *out = nullptr;
-  std::unique_ptr<sphmap_tess> T(new sphmap_tess);
+  std::unique_ptr<sphmap_tess> T = new_tess(ctx);
   int rc = guarded(ctx, [&] {
     SPH_REQUIRE(n >= 1 && n < ((int64_t)1 << 31), SPHMAP_EINVAL, "n out of range [1, 2^31)");
     SPH_REQUIRE(d_generators && h_box_lo && h_box_hi, SPHMAP_EINVAL, "null array");
@@ -269,7 +288,7 @@ int sphmap_tess_build_voronoi(sphmap_ctx *ctx, int64_t n, const double *d_genera
                           as_stream(stream));
   });
   if (rc != SPHMAP_OK) return rc;
-  *out = T.release();
+  *out = made_tess(T);
   return SPHMAP_OK;
 }
 
@@ -307,6 +326,7 @@ int sphmap_tess_free(sphmap_ctx *ctx, sphmap_tess *tess) {
   if (!ctx || !tess) return SPHMAP_EINVAL;
   (void)hipSetDevice(ctx->c.device);
   (void)hipDeviceSynchronize();
+  if (tess->maker == ctx && tess->t.device == ctx->c.device) tess->t.mem.pool = &ctx->c.pool;
   delete tess;
   return SPHMAP_OK;
 }
@@ -423,6 +443,7 @@ int map_particles_to_cells_batch(sphmap_ctx *ctx, int32_t n_inst, const sphmap_t
       while ((int)C.scratch_batch.size() < n_inst) {
         C.scratch_batch.push_back(new sphmap::PairsDev);
         C.scratch_batch.back()->mem.budget = &C.ws;
+        C.scratch_batch.back()->mem.spare = &C.pool;
       }
       for (int k = 0; k < n_inst; ++k) P[k] = C.scratch_batch[k];
     }

@@ -6,6 +6,7 @@
 namespace sphmap {
 
 void *BlockPool::take(size_t bytes, size_t &got) {
+  std::lock_guard<std::mutex> lock(mu);
   auto it = blocks.lower_bound(bytes);
   if (it == blocks.end() || it->first / 2 >= bytes) return nullptr;
   void *p = it->second;
@@ -16,6 +17,7 @@ void *BlockPool::take(size_t bytes, size_t &got) {
 }
 
 void BlockPool::put(void *p, size_t bytes) {
+  std::lock_guard<std::mutex> lock(mu);
   if (held + bytes > cap) {
     (void)hipFree(p);
     return;
@@ -25,6 +27,7 @@ void BlockPool::put(void *p, size_t bytes) {
 }
 
 void BlockPool::trim() {
+  std::lock_guard<std::mutex> lock(mu);
   while (held > cap && !blocks.empty()) {
     auto it = std::prev(blocks.end());
     (void)hipFree(it->second);
@@ -34,6 +37,7 @@ void BlockPool::trim() {
 }
 
 void BlockPool::release() {
+  std::lock_guard<std::mutex> lock(mu);
   for (auto &kv : blocks) (void)hipFree(kv.second);
   blocks.clear();
   held = 0;
@@ -74,10 +78,11 @@ void *Arena::get(const std::string &name, size_t bytes) {
       }
     }
     hipError_t e = hipMalloc(&b.p, want);
-    if (e != hipSuccess && pool && !pool->blocks.empty()) {
+    BlockPool *kept = pool ? pool : spare;
+    if (e != hipSuccess && kept && !kept->blocks.empty()) {
       // the kept blocks first go back to the device
       (void)hipGetLastError();
-      pool->release();
+      kept->release();
       e = hipMalloc(&b.p, want);
     }
     if (e != hipSuccess) {
