@@ -379,8 +379,9 @@ __global__ void __launch_bounds__(kBlock) k_radix_scatter(const K *kin, const in
   }
 }
 
-// At most kOneItems items, all passes in one workgroup: 16 wavefronts of 256
-// items in input order.
+// At most kOneItems items, all passes in one workgroup: 16 wavefronts of up to
+// 256 items in input order, as few as spread the items over all of them (512
+// items by 30 bits: 12 us, 19 with 256 in each of two wavefronts; MI355X).
 template <typename K>
 __global__ void __launch_bounds__(kOneThreads) k_radix_one(K *keys, int32_t *vals, int n, int lo, int hi) {
   constexpr int kW = kOneThreads / 64, kIt = kOneItems / kOneThreads;
@@ -390,13 +391,15 @@ __global__ void __launch_bounds__(kOneThreads) k_radix_one(K *keys, int32_t *val
   __shared__ int32_t sv[kOneItems];
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  const int it = (n + kOneThreads - 1) / kOneThreads, first = w * 64 * it + lane;
   K kk[kIt];
   int32_t vv[kIt];
 #pragma unroll
   for (int j = 0; j < kIt; ++j) {
-    const int i = w * 64 * kIt + j * 64 + lane;
-    kk[j] = i < n ? keys[i] : (K)0;
-    vv[j] = i < n ? vals[i] : 0;
+    const int i = first + j * 64;
+    const bool valid = j < it && i < n;
+    kk[j] = valid ? keys[i] : (K)0;
+    vv[j] = valid ? vals[i] : 0;
   }
   for (int shift = lo; shift < hi; shift += kRadixBits) {
     const int rb = min(kRadixBits, hi - shift);
@@ -406,7 +409,9 @@ __global__ void __launch_bounds__(kOneThreads) k_radix_one(K *keys, int32_t *val
     unsigned rk[kIt];
 #pragma unroll
     for (int j = 0; j < kIt; ++j) {
-      const bool valid = w * 64 * kIt + j * 64 + lane < n;
+      rk[j] = ~0u;
+      if (j >= it) continue;  // uniform
+      const bool valid = first + j * 64 < n;
       const unsigned d = (unsigned)(kk[j] >> shift) & mask;
       const uint64_t peers = digit_peers(valid, d, rb);
       const unsigned r = (unsigned)__popcll(peers & lt);
@@ -450,8 +455,8 @@ __global__ void __launch_bounds__(kOneThreads) k_radix_one(K *keys, int32_t *val
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kIt; ++j) {
-      const int i = w * 64 * kIt + j * 64 + lane;
-      if (i < n) {
+      const int i = first + j * 64;
+      if (j < it && i < n) {
         kk[j] = sk[i];
         vv[j] = sv[i];
       }
@@ -459,8 +464,8 @@ __global__ void __launch_bounds__(kOneThreads) k_radix_one(K *keys, int32_t *val
   }
 #pragma unroll
   for (int j = 0; j < kIt; ++j) {
-    const int i = w * 64 * kIt + j * 64 + lane;
-    if (i < n) {
+    const int i = first + j * 64;
+    if (j < it && i < n) {
       keys[i] = kk[j];
       vals[i] = vv[j];
     }

@@ -21,7 +21,7 @@ def ctx(request):
     c.close()
 
 
-@pytest.mark.parametrize("n", [1, 2, 65, 4095, 4096, 4097, 6143, 131072, 131073])
+@pytest.mark.parametrize("n", [1, 2, 65, 1024, 1025, 3073, 4095, 4096, 4097, 6143, 131072, 131073])
 def test_octree_sort(ctx, n, oracle):
     import paper_2410_15227_amd as pkg
     print("case:", n, flush=True)
