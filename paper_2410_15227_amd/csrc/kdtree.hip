@@ -45,25 +45,40 @@ struct KdNodes {
   double *split;
 };
 
-__global__ void k_kd_check(int64_t n, const double *xyz, const double *m, int *bad, unsigned long long *mmax) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// (one maximum a workgroup of at most kCheckBlocks: one a wavefront, 4,096 on
+// one address, took 53 us for 262,139 particles)
+constexpr int kCheckBlocks = 256;
+__global__ void __launch_bounds__(256) k_kd_check(int64_t n, const double *xyz, const double *m, int *bad,
+                                                  unsigned long long *mmax) {
+  __shared__ unsigned long long part[256 / 64];
   unsigned long long most = 0ull;
-  if (i < n) {
+  int no = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     for (int k = 0; k < 3; ++k) {
       const double x = xyz[3 * i + k];
-      if (!(x >= 0.0 && x < 1.0)) atomicOr(bad, 1);
+      if (!(x >= 0.0 && x < 1.0)) no |= 1;
     }
     const double mi = m[i];
-    if (!(mi > 0.0 && mi < INFINITY)) atomicOr(bad, 2);
-    else most = (unsigned long long)__double_as_longlong(mi);
+    if (!(mi > 0.0 && mi < INFINITY)) {
+      no |= 2;
+    } else {
+      const unsigned long long u = (unsigned long long)__double_as_longlong(mi);
+      if (u > most) most = u;
+    }
   }
-  // one maximum a wavefront: n of them on one address took 53 us for 262,139
+  if (no) atomicOr(bad, no);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const unsigned long long u = __shfl_xor(most, o, 64);
     if (u > most) most = u;
   }
-  if ((threadIdx.x & 63) == 0 && most) atomicMax(mmax, most);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = most;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w)
+      if (part[w] > most) most = part[w];
+    if (most) atomicMax(mmax, most);
+  }
 }
 
 __device__ inline void kd_zero(KdNodes N, int64_t k) {  // before the node's sums
@@ -544,7 +559,7 @@ void kd_pseudo_build(Ctx &ctx, KdArgs &ka, hipStream_t s) {
   unsigned long long *dmax = ar.get<unsigned long long>("kd_mmax", 1);
   SPH_HIP(hipMemsetAsync(bad, 0, sizeof(int), s));
   SPH_HIP(hipMemsetAsync(dmax, 0, sizeof(unsigned long long), s));
-  k_kd_check<<<grid_of(n), 256, 0, s>>>(n, a.xyz, a.m, bad, dmax);
+  k_kd_check<<<std::min<unsigned>(grid_of(n), kCheckBlocks), 256, 0, s>>>(n, a.xyz, a.m, bad, dmax);
   SPH_LAUNCH_CHECK();
   int bad_h = 0;
   unsigned long long mm = 0;
