@@ -732,6 +732,7 @@ __device__ __forceinline__ int newton_step(double sw, double sd, double h, doubl
 constexpr int kNearTiles = 96;
 constexpr int kWideTiles = 2048; // near tiles a workgroup of that kernel can hold
 constexpr int kWideWaves = 16;
+constexpr int kWideKept = 48;    // tiles whose terms it keeps
 constexpr int kNewtonSteps = 30;
 
 // A node handed from the one-wave to the wide Newton kernel.
@@ -835,13 +836,19 @@ __device__ __forceinline__ T sum_to_63(T v) {
   return dpp_add<0x143>(v);
 }
 // inclusive sums over the wavefront's lanes of values whose sums are exact
-__device__ __forceinline__ double wave_incl(double v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const double y = __shfl_up(v, d, 64);
-    if (lane >= d) v += y;
-  }
-  return v;
+template <int kCtrl, int kRows>
+__device__ __forceinline__ double dpp_scan(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRows, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRows, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_incl(double v) {
+  v = dpp_scan<0x111, 0xf>(v);
+  v = dpp_scan<0x112, 0xf>(v);
+  v = dpp_scan<0x114, 0xf>(v);
+  v = dpp_scan<0x118, 0xf>(v);
+  v = dpp_scan<0x142, 0xa>(v);     // into rows 1 and 3
+  return dpp_scan<0x143, 0xc>(v);  // into rows 2 and 3
 }
 
 // Newton for nodes that meet many units, one workgroup a node, its sums bit
@@ -851,17 +858,19 @@ __device__ __forceinline__ double wave_incl(double v, int lane) {
 // additions, which any order gives alike.  So, a step:
 //   - the near tiles are listed in order, and their sums taken in any order
 //     to foresee the binade each tile starts in;
-//   - every tile adds its terms' integers for that binade (the positive and
-//     the negative ones apart, to bound the sums inside it), or is marked
-//     where a term lies half way;
+//   - every tile adds its terms' integers for that binade (and a bound of the
+//     sum of their sizes: dt has both signs, and the sums inside the tile have
+//     to stay in the binade too), or is marked where a term lies half way;
 //   - one wavefront goes through the tiles 64 at a time, adding the integers
 //     up to the first tile that starts in another binade, could leave it, or
 //     is marked; that tile's terms it adds one by one.
 // About 20 to 40 of a step's 980 tiles are added one by one where the sums
-// pass their first binades.  A step over 62,751 units takes 70 us (350 us on
-// one wave); what bounds the kernel is the node with the most steps, 30 that
-// wait for each other: 2.1 ms of a 1,048,576-particle build, whose Newton part
-// was 4.3 ms and is 2.3 (MI355X).
+// pass their first binades; the terms of the marked tiles and of those foreseen
+// to end in another binade are kept in LDS for that.  A step over 62,751 units
+// takes 55 us (350 us on one wave; 70 with the walk's scans by shuffles, two
+// sums a tile for its bounds and no terms kept); what bounds the kernel is the
+// node with the most steps, 30 that wait for each other: 1.6 ms of a
+// 1,048,576-particle build, whose Newton part was 4.3 ms and is 1.8 (MI355X).
 __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode *wide, const int32_t *n_wide, HUnits U,
                                                                 const double *o_xyz, const double *o_s, double hfact,
                                                                 double eps, double *o_h, int32_t *o_branch,
@@ -874,11 +883,15 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
     float2 f;
     double v;
   } tw[kWideTiles];
-  __shared__ double vp[kWideTiles], vn[kWideTiles];       // integers of dt > 0 and of dt < 0
+  __shared__ double vd[kWideTiles];                       // integers of dt
+  __shared__ float va[kWideTiles];                        // bound of the sum of their sizes
   __shared__ int16_t ew[kWideTiles], ed[kWideTiles];      // binades they are in
   __shared__ int wcnt[kWideWaves];
   __shared__ float wsum[2][kWideWaves];
   __shared__ double2 hb[64];
+  __shared__ double2 kept[kWideKept][64];                 // terms of tiles expected to be added one by one
+  __shared__ int8_t slot[kWideTiles];                     // where, -1: nowhere
+  __shared__ int n_kept;
   __shared__ double next_h;
   __shared__ int verdict;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -972,14 +985,25 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
             a += wsum[0][w];
             c += wsum[1][w];
           }
-          tw[j].f = make_float2(a - f0.x - f1.x, c - f0.y - f1.y);
-          tw[j + 1].f = make_float2(a - f1.x, c - f1.y);
+          const float2 s0 = make_float2(a - f0.x - f1.x, c - f0.y - f1.y), s1 = make_float2(a - f1.x, c - f1.y);
+          tw[j].f = s0;
+          tw[j + 1].f = s1;
+          // a tile that ends in another binade than it starts in is not added as integers
+          const auto leaves = [](float2 u, float ex, float ey) {
+            return __builtin_amdgcn_frexp_expf(u.x) != __builtin_amdgcn_frexp_expf(ex) ||
+                   __builtin_amdgcn_frexp_expf(u.y) != __builtin_amdgcn_frexp_expf(ey);
+          };
+          slot[j] = leaves(s0, s1.x, s1.y) ? 1 : 0;
+          slot[j + 1] = leaves(s1, a, c) ? 1 : 0;
+          if (tid == 0) n_kept = 0;
         }
         __syncthreads();
         for (int j = wid; j < T; j += 2 * kWideWaves) {
-          double iw[2], ip[2], in[2];
+          double iw[2], id[2];
+          float sz[2];
           int kw[2], kd[2];
           bool mark[2];
+          int8_t at[2];
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
             const int jq = min(j + q * kWideWaves, T - 1);
@@ -991,26 +1015,36 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
             // in units of the spacing of doubles in [2^(k - 1), 2^k)
             const double rw = ldexp(w, 53 - kw[q]), rd = ldexp(dt, 53 - kd[q]);
             iw[q] = rint(rw);
-            const double id = rint(rd);
-            mark[q] = __ballot(fabs(rw - iw[q]) == 0.5 || fabs(rd - id) == 0.5) != 0ull;
-            ip[q] = fmax(id, 0.0);
-            in[q] = fmin(id, 0.0);
+            id[q] = rint(rd);
+            mark[q] = __ballot(fabs(rw - iw[q]) == 0.5 || fabs(rd - id[q]) == 0.5) != 0ull;
+            sz[q] = (float)fabs(id[q]);
+            at[q] = -1;
+            if (j + q * kWideWaves < T && (mark[q] || slot[jq])) {  // uniform
+              int k = 0;
+              if (lane == 0) k = atomicAdd(&n_kept, 1);
+              k = __builtin_amdgcn_readfirstlane(k);
+              if (k < kWideKept) {
+                kept[k][lane] = make_double2(w, dt);
+                at[q] = (int8_t)k;
+              }
+            }
           }
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
             iw[q] = sum_to_63(iw[q]);
-            ip[q] = sum_to_63(ip[q]);
-            in[q] = sum_to_63(in[q]);
+            id[q] = sum_to_63(id[q]);
+            sz[q] = sum_to_63(sz[q]) * (1.0f + 1e-4f);  // above the exact sum
           }
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
             const int jq = j + q * kWideWaves;
             if (lane == 63 && jq < T) {
               tw[jq].v = iw[q];
-              vp[jq] = ip[q];
-              vn[jq] = in[q];
+              vd[jq] = id[q];
+              va[jq] = sz[q];
               ew[jq] = mark[q] ? kMarked : (int16_t)kw[q];
               ed[jq] = (int16_t)kd[q];
+              slot[jq] = at[q];
             }
           }
         }
@@ -1022,10 +1056,11 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
             const int j = j0 + lane;
             const int kw = __builtin_amdgcn_frexp_exp(sw), kd = __builtin_amdgcn_frexp_exp(sd);
             const bool in = j < T;
-            const double xw = in ? tw[j].v : 0.0, xp = in ? vp[j] : 0.0, xn = in ? vn[j] : 0.0;
-            const double cw = wave_incl(xw, lane), cd = wave_incl(xp + xn, lane);
+            const double xw = in ? tw[j].v : 0.0, xd = in ? vd[j] : 0.0, xa = in ? (double)va[j] : 0.0;
+            const double xp = 0.5 * (xa + xd), xn = 0.5 * (xd - xa);  // bounds of the sums of dt > 0 and of dt < 0
+            const double cw = wave_incl(xw), cd = wave_incl(xd);
             // the sums at the tile's start and the bounds inside it, in units
-            const double bw = ldexp(sw, 53 - kw) + (cw - xw), bd = ldexp(sd, 53 - kd) + (cd - (xp + xn));
+            const double bw = ldexp(sw, 53 - kw) + (cw - xw), bd = ldexp(sd, 53 - kd) + (cd - xd);
             constexpr double kOne = 4503599627370496.0, kTwo = 2.0 * kOne;  // the binade is [kOne, kTwo)
             const bool okw = in && sw > 0.0 && ew[in ? j : 0] == kw && bw >= kOne && bw + xw <= kTwo - 1.0;
             const bool okd = sd > 0.0 ? bd + xn >= kOne + 1.0 && bd + xp <= kTwo - 1.0
@@ -1034,30 +1069,31 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
             const int n = good == ~0ull ? 64 : __builtin_ctzll(~good);  // tiles up to the first that is not
             if (n > 0) {
               sw = ldexp(readlane_d(bw + xw, n - 1), kw - 53);
-              sd = ldexp(readlane_d(bd + (xp + xn), n - 1), kd - 53);
+              sd = ldexp(readlane_d(bd + xd, n - 1), kd - 53);
               j0 += n;
             }
-            if (n < 64 && j0 < T) {  // that tile term by term
-              double w, dt;
-              const bool hit = terms(j0, w, dt);
-              const uint64_t m = __ballot(hit);
-              if (hit) hb[__popcll(m & below)] = make_double2(w, dt);
-              __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-              __builtin_amdgcn_wave_barrier();
-              __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (n < 64 && j0 < T) {  // that tile term by term (terms of 0 change nothing)
+              const int k = __builtin_amdgcn_readfirstlane((int)slot[j0]);
+              const double2 *row = k >= 0 ? kept[k] : hb;
+              if (k < 0) {
+                double w, dt;
+                (void)terms(j0, w, dt);
+                hb[lane] = make_double2(w, dt);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+              }
               double acc = lane == 0 ? sw : sd;
               if (lane < 2) {
-                const double *src = reinterpret_cast<const double *>(hb) + lane;
-                const int cnt = __popcll(m);
-                int k = 0;
-                for (; k + 16 <= cnt; k += 16) {
+                const double *src = reinterpret_cast<const double *>(row) + lane;
+#pragma unroll
+                for (int t = 0; t < 64; t += 16) {
                   double x[16];
 #pragma unroll
-                  for (int u = 0; u < 16; ++u) x[u] = src[2 * (k + u)];
+                  for (int u = 0; u < 16; ++u) x[u] = src[2 * (t + u)];
 #pragma unroll
                   for (int u = 0; u < 16; ++u) acc += x[u];
                 }
-                for (; k < cnt; ++k) acc += src[2 * k];
               }
               sw = readlane_d(acc, 0);
               sd = readlane_d(acc, 1);
