@@ -313,7 +313,7 @@ def main():
                 "kernel": "exact_integral" + (" (k_exact_edges + k_exact_mixed_list"
                                               + (" + k_exact_gather)" if gat_n else ")")
                                               if args.precision == "mixed"
-                                              else " (k_exact_fp64)"),
+                                              else " (k_exact_edges + k_exact_fp64_list)"),
                 "kernel_ms": round(k_avg_s * 1e3, 4), "work_basis": basis,
                 "flop_per_pair": round(flop / max(n_pairs, 1), 1), "trans_per_pair": round(trans / max(n_pairs, 1), 1),
                 "device_flop_per_pair": round(dev_flop / max(n_pairs, 1), 1),
