@@ -1,10 +1,11 @@
 """The device Voronoi builder where its neighbour search and its cells' limits
 work hardest, against the oracle's brute-force cells: a few sites far from a
-dense clump (grid cells are descended into; cells that outgrow 64 planes on
-the way are built again), clumps within clumps, flat and long boxes, a
-lattice, two to five sites, and the same under a workspace cap (a coarser
-site grid).  Volumes and radii within 1e-11 of the cell's own scale, as in
-the builder's other tests."""
+dense clump, clumps within clumps, flat and long boxes, a
+lattice, two to five sites, and the same under a workspace cap (cells
+are not kept between count and fill).  Volumes and radii within 1e-11 of the
+cell's own scale, as in the builder's other tests.  One Lloyd iteration moves
+the sites to the oracle's centroids within 1e-12 of the box, and twice gives
+the same bits."""
 import numpy as np
 import pytest
 
@@ -58,3 +59,23 @@ def test_cells_match_oracle(name, cap, oracle):
     assert abs(vol.sum() / np.prod(hi - lo) - 1.0) < 1e-11
     dt.free()
     ctx.close()
+
+
+@pytest.mark.parametrize("name", ["clump", "nested", "flat", "long", "lattice", "2", "5"])
+def test_lloyd_matches_oracle(name, oracle):
+    import paper_2410_15227_amd as pkg
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("case: lloyd", name, flush=True)
+    g, lo, hi = sites(name)
+    if np.diff(oracle.voronoi(g, lo, hi)["cell_face_off"]).max() > 64:
+        pytest.skip("refused: more than 58 neighbours")
+    ctx = pkg.Context(0)
+    got = []
+    for _ in range(2):
+        dt, out = pkg.build_voronoi(ctx, g, lo, hi, n_lloyd=1)
+        got.append(out.cpu().numpy())
+        dt.free()
+    ctx.close()
+    assert np.array_equal(got[0], got[1])
+    assert np.abs(got[0] - oracle.lloyd(g, 1, lo, hi)).max() < 1e-12 * (hi - lo).max()
