@@ -25,11 +25,13 @@
 // |h_new - h| / h0 < eps_h; Newton fails after 30 steps, when an iterate
 // leaves [1e-2 h0, 1e2 h0] or when |f'| < 1e-12; then bisection on
 // [1e-2 h0, 1e2 h0] when f changes sign there, else h0.  Newton's sums over
-// units run in unit order, one wavefront per pseudo-particle; the nodes it
-// leaves go to a second kernel, 16 wavefronts per node, whose bracket and
-// bisection steps decide from fixed-order tree sums (falling back to the
-// unit-order sums within their rounding margin), so every decision is that
-// of the unit-order sums.
+// units are those of unit order: one wavefront per pseudo-particle, or a
+// workgroup where the node meets many units (the same sums, bit for bit).
+// The nodes Newton leaves go to a third kernel, 16 wavefronts per node, whose
+// bracket and bisection steps decide from bounds of 64-unit boxes, then from
+// fixed-order tree sums in binary32, then from the unit-order sums, each
+// where the one before leaves the sign within its rounding margin, so every
+// decision is that of the unit-order sums.
 #include "common.hpp"
 
 namespace sphmap {
