@@ -22,7 +22,7 @@
 // positions of twin vertices and for handing new vertices to their slots.
 // (With the vertices compacted and T rebuilt after each cut, and shuffles
 // for the scans and sums, 131,071 turbulent sites took 5.95 ms a
-// construction; now 2.7 ms, about 9,000 wave instructions a cell at 0.62
+// construction; now 2.4 ms, about 8,400 wave instructions a cell at 0.61
 // lane utilisation, most of them vector issue, of 64 lanes for about 25
 // vertices.)
 //
@@ -37,16 +37,16 @@
 // the mixed path's rounding follows that numbering, and a site that moves by
 // its last bit changes which of the mixed path's thresholds its faces meet
 // (up to 1e-7 of a cell's mass).  Nested grids of Morton runs took the sites
-// of a Lloyd iteration nearest first, 1.4 to 1.9 ms each instead of 2.7, but
+// of a Lloyd iteration nearest first, 1.4 to 1.9 ms each instead of 2.6, but
 // left sites that differ by an ulp; Lloyd iterations therefore share the fixed
 // order, and add a cell's tetrahedra in the order of its vertices' numbers.
 // Vertices carry their age (the cut that made them, and their place in it),
 // so that slots reused in any order still give the numbering of a list that
 // only closes up and grows.
 //
-// Outputs: centroids (Lloyd iterations); face, face vertex and
-// vertex counts; the faces themselves (each face's vertex cycle walked
-// through T) with the neighbour each one faces.
+// Outputs: centroids (Lloyd iterations); face, face vertex and vertex counts;
+// the faces themselves (each face's vertex cycle walked through T) with the
+// neighbour each one faces.
 #include "common.hpp"
 
 namespace sphmap {
@@ -54,7 +54,14 @@ namespace {
 
 constexpr int kVP = 64;     // planes per cell: 6 box planes + neighbours
 constexpr int kVT = 128;    // vertices per cell
-constexpr int kVWaves = 4;  // cells per workgroup
+// Cells per workgroup.  One, so that the room of a cell that is done goes to
+// the next at once, whatever its neighbours still cut (131,071 sites with 5
+// iterations: 19.6 ms with four, 19.2 with two, 18.1 with one).
+constexpr int kVWaves = 1;
+// Of the 64 nearest sites about 22 cut; the others cost a dependent step
+// each.  After this many the rest are tested at once, one a lane (131,071
+// sites with 5 iterations: 17.2 ms without, 16.9 at 12 or 16, 17.2 at 24).
+constexpr int kVAhead = 12;
 constexpr int kVRing = 128;  // sites in a group beyond which its grid cells are tested before them
 
 // error bits
@@ -357,6 +364,15 @@ __device__ inline int rcell(double x, double lo, double cs, int G) {
   return min(max(i, 0), G - 1);
 }
 
+// Whether the plane n.x <= d (a lane's) cuts any vertex.
+__device__ inline bool vcuts(const VorLds &L, const VorCell &C, double nx, double ny, double nz, double d, double eps) {
+  bool cuts = false;
+  const int nT = vslots(C);
+#pragma unroll 2
+  for (int t = 0; t < nT; ++t) cuts |= nx * L.vx[t] + ny * L.vy[t] + nz * L.vz[t] - d > eps;
+  return cuts;
+}
+
 // Cut by the bisectors of one batch of candidates (lane: the vector to the
 // site, its distance and its index), nearest first.  With `test`, the planes
 // are first tested against every vertex, one candidate per lane, so that the
@@ -374,11 +390,7 @@ __device__ bool vbatch(VorLds &L, VorCell &C, bool cand, double ex, double ey, d
   const double nx = ex / dist, ny = ey / dist, nz = ez / dist;
   const double dd = 0.5 * dist;
   if (test) {
-    bool cuts = false;
-    const int nT = vslots(C);
-#pragma unroll 2
-    for (int t = 0; t < nT; ++t) cuts |= nx * L.vx[t] + ny * L.vy[t] + nz * L.vz[t] - dd > eps;
-    cand = cand && cuts;
+    cand = vcuts(L, C, nx, ny, nz, dd, eps) && cand;
     cm = ballot64(cand);
     if (!cm) return true;
   }
@@ -516,8 +528,8 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
                        double eps, int lane, int &err) {
   const int off = vscan_excl(cnt);
   const int tot = __builtin_amdgcn_readlane(off + cnt, 63);
+  uint64_t best = ~0ull;
   if (nearest) {
-    uint64_t best = ~0ull;
     // the home cell (lane 13 of the 27) first, for a tight bound
     const int home0 = __builtin_amdgcn_readlane(off, 13), home1 = home0 + __builtin_amdgcn_readlane(cnt, 13);
     for (int turn = 0; turn < 2; ++turn)
@@ -549,19 +561,32 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
       ez = Gd.gen[3 * (int64_t)j + 2] - gz;
       dist = sqrt(ex * ex + ey * ey + ez * ez);
     }
-    const int nb = __popcll(ballot64(some));
     if (ballot64(some && !(dist > 0.0))) {
       err = kErrCoincident;
       return false;
     }
     const double nx = ex / dist, ny = ey / dist, nz = ez / dist, dd = 0.5 * dist;
-    for (int l = 0; l < nb; ++l) {
+    uint64_t todo = ballot64(some);
+    for (int at = 0; todo; todo &= todo - 1, ++at) {
+      if (at == kVAhead) {  // the rest at once: a plane that cuts no vertex cuts none of a smaller cell's
+        todo &= ballot64(vcuts(L, C, nx, ny, nz, dd, eps));
+        if (!todo) break;
+      }
+      const int l = __builtin_ctzll(todo);
       const double dl = readlane_d(dd, l);
       if (dl > C.R + eps) break;
       if (!vcut(L, C, readlane_d(nx, l), readlane_d(ny, l), readlane_d(nz, l), dl, __builtin_amdgcn_readlane(j, l),
                 eps, lane, err))
         return false;
     }
+  }
+  // the nearest are done with: what they left cuts nothing a second time
+  // (tested again with the others: 18.1 ms in place of 17.2)
+  uint64_t upto = 0ull;
+  if (nearest) {
+    if (tot <= 64) return true;
+    upto = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best, 63) |
+           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(best >> 32), 63) << 32);
   }
   bool reach = cnt > 0;
   if (reach && tot > kVRing)
@@ -580,7 +605,7 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
       cand = 0.5 * dist <= C.R + eps;
       if (cand) {
         j = Gd.sorted[k];
-        cand = j != c;
+        cand = j != c && (((uint64_t)__float_as_uint((float)dist) << 32) | (uint32_t)j) > upto;
       }
     }
     if (!vbatch(L, C, cand, ex, ey, ez, dist, j, true, eps, lane, err)) return false;
