@@ -743,6 +743,12 @@ struct WideNode {
   double h;       // the next step's length
 };
 
+// Lengths from which the bracket takes binary32 sums: squares of distances
+// below 2e-19 underflow there, which moves x by 2e-8 at most for these (and
+// 1 / he is finite).  Shorter ones, of nodes at the corner of the box, take
+// the binary64 sums.
+constexpr double kLeast32 = 1e-11;
+
 constexpr int kHWaves = 4;    // pseudo-particles per workgroup in the Newton kernel
 constexpr int kBWaves = 16;   // wavefronts per pseudo-particle in the bracket kernel
 
@@ -1146,7 +1152,7 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
 // the tiles' boxes decide, w falling with distance (sw lies between the sums
 // of each tile's count times w at its farthest and at its nearest point), for
 // a 64th of the work; and nearly all the others binary32 sums within their
-// error.  The last part of a 1,048,576-particle build took 1.83 ms with
+// error (he above kLeast32).  The last part of a 1,048,576-particle build took 1.83 ms with
 // binary64 sums at every step, 0.68 ms with the boxes, 0.41 ms now (MI355X).
 __global__ void __launch_bounds__(64 * kBWaves) k_hsolve_bracket(const int32_t *fails, const int32_t *n_fails,
                                                                 HUnits U, const double *o_xyz, const double *o_s,
@@ -1216,7 +1222,7 @@ __global__ void __launch_bounds__(64 * kBWaves) k_hsolve_bracket(const int32_t *
         least += __shfl_xor(least, o, 64);
       }
       decide(least * (1.0 - 1e-9), most * (1.0 + 1e-9));
-      if (!known) {
+      if (!known && he > kLeast32) {
         // binary32 terms of the near tiles, t = wid mod kBWaves: x within 8e-7,
         // |w'| <= 1, so w within 4e-6; a lane's sum of its tiles within 1e-5
         const int lane = threadIdx.x & 63;
