@@ -409,4 +409,13 @@ size_t interp_scratch_bound(int64_t n, int64_t ne);
 
 inline int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Workgroups of 256 for a kernel that steps through `lanes` items: twice what
+// the chip holds at most, so that a launch stays far below the 2^32 work-items
+// it may have, whatever the count.
+constexpr int64_t kStridedBlocks = 4096;
+inline unsigned strided_blocks(int64_t lanes) {
+  const int64_t b = div_up(lanes, 256);
+  return (unsigned)(b < kStridedBlocks ? b : kStridedBlocks);
+}
+
 }  // namespace sphmap

@@ -73,15 +73,17 @@ __device__ inline int digit_of(uint64_t key, int level) {
 }
 
 // A level's nodes are [lv[0], lv[1]), at most nb; eight lanes a node, one for
-// each octant d.
+// each octant d, lane t & 7 of node t >> 3.  The launches step through the
+// level (strided_blocks): nb is a bound of up to n, and eight lanes each of
+// 2^29 nodes are more than one launch takes.
 struct Octant {
   int32_t first, count;  // the octant's run of the node's particles
   uint32_t some;         // bit per octant: not empty
   int64_t node;          // -1: no node
 };
-__device__ __forceinline__ Octant octant_of(const NodeArrays &N, const int64_t *lv, int64_t nb, int level,
+__device__ __forceinline__ Octant octant_of(const NodeArrays &N, const int64_t *lv, int64_t nb, int64_t t, int level,
                                             const uint64_t *keys, int leaf_max, int max_depth) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, j = t >> 3;
+  const int64_t j = t >> 3;
   const int d = (int)t & 7, lane = threadIdx.x & 63;
   Octant o{0, 0, 0u, j < nb && lv[0] + j < lv[1] ? lv[0] + j : -1};
   int32_t f = 0, a = 0;
@@ -109,9 +111,11 @@ __device__ __forceinline__ Octant octant_of(const NodeArrays &N, const int64_t *
 // children per node of the level
 __global__ void k_split(NodeArrays N, const int64_t *lv, int64_t nb, int level, const uint64_t *keys, int leaf_max,
                         int max_depth, int64_t *nch) {
-  const Octant o = octant_of(N, lv, nb, level, keys, leaf_max, max_depth);
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if ((t & 7) == 0 && (t >> 3) < nb) nch[t >> 3] = __popc(o.some);
+  for (int64_t t0 = (int64_t)blockIdx.x * 256; t0 < 8 * nb; t0 += (int64_t)gridDim.x * 256) {
+    const int64_t t = t0 + threadIdx.x;
+    const Octant o = octant_of(N, lv, nb, t, level, keys, leaf_max, max_depth);
+    if ((t & 7) == 0 && (t >> 3) < nb) nch[t >> 3] = __popc(o.some);
+  }
 }
 
 // The children and the next level's range; where they do not fit in cap nodes
@@ -121,28 +125,30 @@ __global__ void k_children(NodeArrays N, int64_t *lv, int64_t *lacking, int64_t 
                            const uint64_t *keys, int leaf_max, int max_depth, const int64_t *choff) {
   const int64_t next = lv[1], total = choff[nb];
   const bool fits = next + total <= cap;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t == 0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     lv[2] = fits ? next + total : next;
     if (!fits) *lacking = total;
   }
   if (!fits) return;
-  const Octant o = octant_of(N, lv, nb, level, keys, leaf_max, max_depth);
-  if (o.node < 0) return;
-  const int d = (int)t & 7;
-  const int64_t first = next + choff[t >> 3];
-  if (d == 0) {
-    N.nchild[o.node] = __popc(o.some);
-    N.child_first[o.node] = o.some ? (int32_t)first : -1;
-  }
-  if ((o.some >> d) & 1u) {
-    const int64_t cid = first + __popc(o.some & ((1u << d) - 1u));
-    N.first[cid] = o.first;
-    N.count[cid] = o.count;
-    N.parent[cid] = (int32_t)o.node;
-    N.level[cid] = level + 1;
-    N.child_first[cid] = -1;
-    N.nchild[cid] = 0;
+  for (int64_t t0 = (int64_t)blockIdx.x * 256; t0 < 8 * (next - lv[0]); t0 += (int64_t)gridDim.x * 256) {
+    const int64_t t = t0 + threadIdx.x;
+    const Octant o = octant_of(N, lv, nb, t, level, keys, leaf_max, max_depth);
+    if (o.node < 0) continue;
+    const int d = (int)t & 7;
+    const int64_t first = next + choff[t >> 3];
+    if (d == 0) {
+      N.nchild[o.node] = __popc(o.some);
+      N.child_first[o.node] = o.some ? (int32_t)first : -1;
+    }
+    if ((o.some >> d) & 1u) {
+      const int64_t cid = first + __popc(o.some & ((1u << d) - 1u));
+      N.first[cid] = o.first;
+      N.count[cid] = o.count;
+      N.parent[cid] = (int32_t)o.node;
+      N.level[cid] = level + 1;
+      N.child_first[cid] = -1;
+      N.nchild[cid] = 0;
+    }
   }
 }
 
@@ -1481,10 +1487,10 @@ void pseudo_build(Ctx &ctx, PseudoArgs &a, hipStream_t s) {
       const int64_t room = ctx.ws.limit ? nb : n;  // no growth between the launches of a run
       int64_t *nch = ar.get<int64_t>("ps_nch", room + 1);
       int64_t *choff = ar.get<int64_t>("ps_choff", room + 1);
-      k_split<<<(unsigned)div_up(8 * nb, 256), 256, 0, s>>>(G.N, lv + 1 + d, nb, d, keys, o.leaf_max, o.max_depth, nch);
+      k_split<<<strided_blocks(8 * nb), 256, 0, s>>>(G.N, lv + 1 + d, nb, d, keys, o.leaf_max, o.max_depth, nch);
       SPH_LAUNCH_CHECK();
       scan_exclusive_i64(ar, nch, choff, nb, true, s);
-      k_children<<<(unsigned)div_up(8 * nb, 256), 256, 0, s>>>(G.N, lv + 1 + d, lv, nb, G.cap, d, keys, o.leaf_max,
+      k_children<<<strided_blocks(8 * nb), 256, 0, s>>>(G.N, lv + 1 + d, lv, nb, G.cap, d, keys, o.leaf_max,
                                                               o.max_depth, choff);
       SPH_LAUNCH_CHECK();
     }
