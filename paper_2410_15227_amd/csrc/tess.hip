@@ -175,10 +175,11 @@ constexpr int kPrepThreads = 256;
 constexpr int kPrepCells = 8;
 constexpr int kPrepFaces = kPrepThreads;
 constexpr int kPrepSlots = 1024;
+constexpr int64_t kPrepBlocks = 1 << 16;  // workgroups of a launch: a grid of 2^27 cells is past what one takes
 
-__global__ void __launch_bounds__(kPrepThreads) k_tess_prep(int64_t C, const double *gen, const double *vert,
-                                                           const int64_t *cfo, const int64_t *fvo, const int32_t *fv,
-                                                           TessOut T) {
+__global__ void __launch_bounds__(kPrepThreads) k_tess_prep(int64_t first, int64_t C, const double *gen,
+                                                           const double *vert, const int64_t *cfo, const int64_t *fvo,
+                                                           const int32_t *fv, TessOut T) {
   __shared__ double px[kPrepSlots], py[kPrepSlots], pz[kPrepSlots];
   __shared__ uint8_t slot_face[kPrepSlots];
   __shared__ double fn[3][kPrepFaces], fvol[kPrepFaces];
@@ -187,7 +188,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_tess_prep(int64_t C, const dou
   __shared__ bool frev[kPrepFaces];
   __shared__ uint8_t fcell[kPrepFaces];
   const int tid = threadIdx.x;
-  const int64_t c0 = (int64_t)blockIdx.x * kPrepCells, c1 = min(C, c0 + kPrepCells);
+  const int64_t c0 = first + (int64_t)blockIdx.x * kPrepCells, c1 = min(C, c0 + kPrepCells);
   const int64_t f0 = cfo[c0], f1 = cfo[c1];
   const int64_t s0 = fvo[f0], s1 = fvo[f1];
   if (f1 - f0 <= kPrepFaces && s1 - s0 <= kPrepSlots) {
@@ -406,11 +407,13 @@ void tess_prepare(Ctx &ctx, TessDev &t, hipStream_t s) {
   SPH_HIP(hipMemsetAsync(bad, 0, sizeof(int), s));
   k_face_cell<<<(unsigned)div_up(C, 256), 256, 0, s>>>(t.cell_face_off, C, t.face_cell);
   SPH_LAUNCH_CHECK();
-  k_tess_prep<<<(unsigned)div_up(C, kPrepCells), kPrepThreads, 0, s>>>(
-      C, t.gen, t.vert, t.cell_face_off, t.face_vtx_off, t.face_vtx,
-      TessOut{t.fplane, t.fsphere, t.fvpos, t.fvpos32, t.fplane32, t.edgeA, t.edgeE, t.edgeM, t.volume, t.radius,
-              t.gen32, bad});
-  SPH_LAUNCH_CHECK();
+  const TessOut to{t.fplane, t.fsphere, t.fvpos,  t.fvpos32, t.fplane32, t.edgeA,
+                   t.edgeE,  t.edgeM,   t.volume, t.radius,  t.gen32,    bad};
+  for (int64_t c = 0; c < C; c += kPrepBlocks * kPrepCells) {
+    k_tess_prep<<<(unsigned)std::min(div_up(C - c, kPrepCells), kPrepBlocks), kPrepThreads, 0, s>>>(
+        c, C, t.gen, t.vert, t.cell_face_off, t.face_vtx_off, t.face_vtx, to);
+    SPH_LAUNCH_CHECK();
+  }
   // cells in Morton order of their sites (locality of the pair search)
   uint64_t *keys = t.mem.get<uint64_t>("cell_keys", C);
   morton_keys(t.gen, 3, C, t.box_lo[0], t.box_lo[1], t.box_lo[2], t.box_size, keys, t.cell_order, s);
