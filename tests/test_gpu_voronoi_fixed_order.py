@@ -1,0 +1,83 @@
+"""The Voronoi builder's arrays as they are exported: the order of the cuts
+numbers faces and vertices, and the mixed mapping's rounding follows it, so
+the arrays are held bit for bit to digests that the builder's first, serial
+search gave (tests/golden/voronoi_digests.json).  Beside them each cell's
+neighbours and radius against the oracle's brute-force cells: a face the
+oracle gives more than 1e-9 of the cell's largest has to be there, and the
+radius is the farthest vertex to a binary32 rounding.  No other neighbour may
+be there."""
+import hashlib
+import json
+import os
+
+import numpy as np
+import pytest
+
+from test_gpu_voronoi_search import sites
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "voronoi_digests.json")
+
+
+def inputs(name):
+    if name == "squares":  # sites crowd towards the box's low walls
+        g = np.random.default_rng(4).random((20011, 3))
+        return g * g, np.zeros(3), np.ones(3)
+    return sites(name)
+
+
+def digest(dt, final_sites):
+    t = dt.export()
+    h = hashlib.sha256()
+    for a in (t.generators, t.vertices, t.cell_face_off, t.face_vtx_off, t.face_vtx, t.face_nbr,
+              final_sites.cpu().numpy()):
+        h.update(np.ascontiguousarray(a).tobytes())
+    return h.hexdigest()
+
+
+@pytest.fixture(scope="module")
+def contexts():
+    import paper_2410_15227_amd as pkg
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    free, capped = pkg.Context(0), pkg.Context(0, workspace_bytes=8 << 30)
+    yield dict(free=free, capped=capped)
+    free.close()
+    capped.close()
+
+
+@pytest.mark.parametrize("which", ["free", "capped"])
+@pytest.mark.parametrize("lloyd", [0, 1, 5])
+@pytest.mark.parametrize("name", ["clump", "nested", "flat", "long", "lattice", "2", "5", "3000", "squares"])
+def test_arrays_of_the_first_search(contexts, which, name, lloyd):
+    import paper_2410_15227_amd as pkg
+    print("case: digest", which, name, lloyd, flush=True)
+    with open(GOLDEN) as f:
+        want = json.load(f)[f"{name}/{lloyd}"]
+    g, lo, hi = inputs(name)
+    dt, final_sites = pkg.build_voronoi(contexts[which], g, lo, hi, n_lloyd=lloyd)
+    got = digest(dt, final_sites)
+    dt.free()
+    assert got == want
+
+
+@pytest.mark.parametrize("name", ["clump", "nested", "flat", "long", "2", "5", "700"])
+def test_neighbours_and_radii_match_oracle(contexts, name, oracle):
+    import paper_2410_15227_amd as pkg
+    print("case: neighbours", name, flush=True)
+    g, lo, hi = inputs(name)
+    want = oracle.voronoi(g, lo, hi)
+    dt, _ = pkg.build_voronoi(contexts["free"], g, lo, hi, n_lloyd=0)
+    t = dt.export()
+    rad = dt.cell_info()[1].cpu().numpy().astype(np.float64)
+    dt.free()
+    for c in range(len(g)):
+        got = set(t.face_nbr[t.cell_face_off[c]:t.cell_face_off[c + 1]].tolist())
+        o = slice(want["cell_face_off"][c], want["cell_face_off"][c + 1])
+        ids, area = want["face_id"][o], want["face_area"][o]
+        assert set(ids[area > 1e-9 * area.max()].tolist()) <= got, c
+        assert got <= set(ids.tolist()), c
+        pts = want["face_pts"][want["face_vtx_off"][o.start]:want["face_vtx_off"][o.stop]]
+        far = np.sqrt(((pts - g[c]) ** 2).sum(1).max())
+        assert abs(rad[c] - far) <= 2.0 ** -22 * far + 1e-12, c
