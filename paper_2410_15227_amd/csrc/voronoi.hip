@@ -406,7 +406,10 @@ __device__ bool vbatch(VorLds &L, VorCell &C, bool cand, double ex, double ey, d
   for (int i = 0; i < nc; ++i) {
     const int l = __builtin_ctzll(ballot64(rank == i));
     const double dl = readlane_d(dd, l);
-    if (dl > C.R + eps) break;
+    if (dl > C.R + eps) {
+      if (!ballot64(rank > i && !(dd > C.R + eps))) break;  // (where keys are equal a nearer one may follow)
+      continue;
+    }
     if (!vcut(L, C, readlane_d(nx, l), readlane_d(ny, l), readlane_d(nz, l), dl, __builtin_amdgcn_readlane(id, l), eps,
               lane, err))
       return false;
@@ -505,6 +508,16 @@ __device__ inline uint64_t vmerge64(uint64_t best, uint64_t chunk, int lane) {
   return key;
 }
 
+// A site's distance and key: the binary32 distance, then the index.  Each in
+// one place and in stated operations, so that a site's key is the same
+// wherever it is formed.
+__device__ __forceinline__ double vdist(double ex, double ey, double ez) {
+  return sqrt(fma(ez, ez, fma(ex, ex, ey * ey)));
+}
+__device__ __forceinline__ uint64_t vkey(double dist, int32_t j) {
+  return ((uint64_t)__float_as_uint((float)dist) << 32) | (uint32_t)j;
+}
+
 // Sites w0 .. w0 + 63 of a group of grid cells (lane: sites s0 .. s0 + cnt of
 // the sorted array at offset off of the group's tot sites): this lane's, or -1.
 __device__ inline int vwindow(VorLds &L, int s0, int cnt, int off, int tot, int w0, int lane) {
@@ -529,6 +542,7 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
   const int off = vscan_excl(cnt);
   const int tot = __builtin_amdgcn_readlane(off + cnt, 63);
   uint64_t best = ~0ull;
+  bool again = false;
   if (nearest) {
     // the home cell (lane 13 of the 27) first, for a tight bound
     const int home0 = __builtin_amdgcn_readlane(off, 13), home1 = home0 + __builtin_amdgcn_readlane(cnt, 13);
@@ -539,7 +553,8 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
         const uint64_t last = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best, 63) |
                               ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(best >> 32), 63) << 32);
         if (last != ~0ull) {
-          const double far = (double)__uint_as_float((uint32_t)(last >> 32)) * (1.0 + 1e-6);
+          // (the cells' walls are rounded, by less than eps)
+          const double far = (double)__uint_as_float((uint32_t)(last >> 32)) * (1.0 + 1e-6) + eps;
           if (!ballot64(off < w0 + 64 && off + cnt > w0 && near2 <= far * far)) continue;
         }
         const int k = vwindow(L, s0, cnt, off, tot, w0, lane);
@@ -548,7 +563,7 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
           const double ex = Gd.x[3 * (int64_t)k] - gx, ey = Gd.x[3 * (int64_t)k + 1] - gy,
                        ez = Gd.x[3 * (int64_t)k + 2] - gz;
           const int32_t j = Gd.sorted[k];
-          if (j != c) key = ((uint64_t)__float_as_uint((float)sqrt(ex * ex + ey * ey + ez * ez)) << 32) | (uint32_t)j;
+          if (j != c) key = vkey(vdist(ex, ey, ez), j);
         }
         if (ballot64(key < last)) best = vmerge64(best, vsort64(key, lane), lane);
       }
@@ -559,7 +574,7 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
       ex = Gd.gen[3 * (int64_t)j] - gx;
       ey = Gd.gen[3 * (int64_t)j + 1] - gy;
       ez = Gd.gen[3 * (int64_t)j + 2] - gz;
-      dist = sqrt(ex * ex + ey * ey + ez * ez);
+      dist = vdist(ex, ey, ez);
     }
     if (ballot64(some && !(dist > 0.0))) {
       err = kErrCoincident;
@@ -579,11 +594,14 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
                 eps, lane, err))
         return false;
     }
+    // past the first that is too far only one with an equal key may cut: then
+    // all of them are tested again
+    again = (todo & ballot64(!(dd > C.R + eps))) != 0ull;
   }
   // the nearest are done with: what they left cuts nothing a second time
   // (tested again with the others: 18.1 ms in place of 17.2)
   uint64_t upto = 0ull;
-  if (nearest) {
+  if (nearest && !again) {
     if (tot <= 64) return true;
     upto = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best, 63) |
            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(best >> 32), 63) << 32);
@@ -601,11 +619,11 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
       ex = Gd.x[3 * (int64_t)k] - gx;
       ey = Gd.x[3 * (int64_t)k + 1] - gy;
       ez = Gd.x[3 * (int64_t)k + 2] - gz;
-      dist = sqrt(ex * ex + ey * ey + ez * ez);
+      dist = vdist(ex, ey, ez);
       cand = 0.5 * dist <= C.R + eps;
       if (cand) {
         j = Gd.sorted[k];
-        cand = j != c && (((uint64_t)__float_as_uint((float)dist) << 32) | (uint32_t)j) > upto;
+        cand = j != c && vkey(dist, j) > upto;
       }
     }
     if (!vbatch(L, C, cand, ex, ey, ez, dist, j, true, eps, lane, err)) return false;

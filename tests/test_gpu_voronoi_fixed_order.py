@@ -81,3 +81,25 @@ def test_neighbours_and_radii_match_oracle(contexts, name, oracle):
         pts = want["face_pts"][want["face_vtx_off"][o.start]:want["face_vtx_off"][o.stop]]
         far = np.sqrt(((pts - g[c]) ** 2).sum(1).max())
         assert abs(rad[c] - far) <= 2.0 ** -22 * far + 1e-12, c
+
+
+def test_equal_binary32_distances(contexts, oracle):
+    """Two sites whose distances round to the same binary32 value, the one that
+    comes first too far to cut and the next just near enough: a corner of the
+    cell is cut off 2e-8 of its distance, 1e5 times the builder's tolerance."""
+    import paper_2410_15227_amd as pkg
+    print("case: equal binary32 distances", flush=True)
+    a, d = 0.29001, 2e-8
+    axes = [[a, 0, 0], [-a, 0, 0], [0, a, 0], [0, -a, 0], [0, 0, a], [0, 0, -a]]
+    g = 0.5 + np.array([[0.0, 0.0, 0.0]] + axes + [[-a * (1 + d)] * 3, [a * (1 - d)] * 3])
+    dist = np.linalg.norm(g - g[0], axis=1)
+    assert dist[7] > dist[8] and np.float32(dist[7]) == np.float32(dist[8])
+    want = oracle.voronoi(g)
+    assert 8 in want["face_id"][:want["cell_face_off"][1]]
+    for c in contexts.values():
+        dt, _ = pkg.build_voronoi(c, g, n_lloyd=0)
+        t = dt.export()
+        dt.free()
+        for c0, c1 in ((0, 8), (8, 0)):
+            assert c1 in t.face_nbr[t.cell_face_off[c0]:t.cell_face_off[c0 + 1]]
+        assert 7 not in t.face_nbr[:t.cell_face_off[1]]
