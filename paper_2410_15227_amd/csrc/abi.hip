@@ -143,7 +143,7 @@ int sphmap_create(int32_t device, size_t workspace_bytes, sphmap_ctx **out) {
   int rc = guarded(ctx.get(), [&] {
     size_t free_b = 0, total_b = 0;
     SPH_HIP(hipMemGetInfo(&free_b, &total_b));
-    ctx->c.pool.cap = total_b / 8;
+    (void)ctx->c.pool.set_cap(total_b / 8);
     // this device's address of the fixed scratch of the no-allocation entry point
     (void)sphmap::noalloc_scratch_init(device);
     ctx->c.d_counters = ctx->c.arena.get<int64_t>("counters", 8);
@@ -569,8 +569,7 @@ int sphmap_set_pool_limit(sphmap_ctx *ctx, uint64_t bytes) {
   if (!ctx) return SPHMAP_EINVAL;
   return guarded(ctx, [&] {
     sphmap::BlockPool &pool = ctx->c.pool;
-    pool.cap = (size_t)bytes;
-    if (pool.held > pool.cap) {
+    if (pool.set_cap((size_t)bytes)) {
       SPH_HIP(hipDeviceSynchronize());
       pool.trim();
     }

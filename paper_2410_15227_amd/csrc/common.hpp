@@ -56,8 +56,9 @@ struct BlockPool {
   size_t cap = 0;
   void *take(size_t bytes, size_t &got);
   void put(void *p, size_t bytes);
+  bool set_cap(size_t bytes);  // whether more is kept
   void trim();  // frees the largest blocks until the kept total is within cap
-  void release();
+  bool release();  // frees every block; whether there was one
   ~BlockPool() { release(); }
 };
 

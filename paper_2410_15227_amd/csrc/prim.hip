@@ -26,6 +26,12 @@ void BlockPool::put(void *p, size_t bytes) {
   held += bytes;
 }
 
+bool BlockPool::set_cap(size_t bytes) {
+  std::lock_guard<std::mutex> lock(mu);
+  cap = bytes;
+  return held > cap;
+}
+
 void BlockPool::trim() {
   std::lock_guard<std::mutex> lock(mu);
   while (held > cap && !blocks.empty()) {
@@ -36,11 +42,13 @@ void BlockPool::trim() {
   }
 }
 
-void BlockPool::release() {
+bool BlockPool::release() {
   std::lock_guard<std::mutex> lock(mu);
+  const bool any = !blocks.empty();
   for (auto &kv : blocks) (void)hipFree(kv.second);
   blocks.clear();
   held = 0;
+  return any;
 }
 
 void *Arena::get(const std::string &name, size_t bytes) {
@@ -79,12 +87,9 @@ void *Arena::get(const std::string &name, size_t bytes) {
     }
     hipError_t e = hipMalloc(&b.p, want);
     BlockPool *kept = pool ? pool : spare;
-    if (e != hipSuccess && kept && !kept->blocks.empty()) {
-      // the kept blocks first go back to the device
-      (void)hipGetLastError();
-      kept->release();
-      e = hipMalloc(&b.p, want);
-    }
+    if (e != hipSuccess) (void)hipGetLastError();
+    // the kept blocks first go back to the device
+    if (e != hipSuccess && kept && kept->release()) e = hipMalloc(&b.p, want);
     if (e != hipSuccess) {
       b.p = nullptr;
       b.bytes = 0;
