@@ -92,7 +92,18 @@ struct Arena {
   T *get(const std::string &name, size_t count) {
     return (T *)get(name, count * sizeof(T) + 16);
   }
-  void release();
+  // the same, nullptr where memory is short
+  template <typename T>
+  T *get_if(const std::string &name, size_t count) {
+    try {
+      return get<T>(name, count);
+    } catch (const Error &e) {
+      if (e.code != SPHMAP_ENOMEM) throw;
+      return nullptr;
+    }
+  }
+  // idle: no queued work uses the blocks, which a pool then takes without a wait
+  void release(bool idle = false);
   ~Arena() { release(); }
 };
 

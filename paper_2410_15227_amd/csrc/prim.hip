@@ -102,14 +102,14 @@ void *Arena::get(const std::string &name, size_t bytes) {
   return b.p;
 }
 
-void Arena::release() {
+void Arena::release(bool idle) {
   if (region) {  // carved from a region this arena does not own
     bufs.clear();
     region_used = 0;
     return;
   }
   // pooled blocks are handed out again at once: queued work must be done
-  if (pool && !bufs.empty()) (void)hipDeviceSynchronize();
+  if (pool && !idle && !bufs.empty()) (void)hipDeviceSynchronize();
   for (auto &kv : bufs) {
     if (!kv.second.p) continue;
     if (budget) budget->held -= kv.second.bytes;

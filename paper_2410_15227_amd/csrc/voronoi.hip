@@ -1079,10 +1079,13 @@ void voronoi_build(Ctx &ctx, TessDev &t, int64_t n, const double *d_gen, const d
           *cv = ar.get<int64_t>("vo_cv", n + 1);
   int64_t *sf = ar.get<int64_t>("vo_sf", n + 1), *sp = ar.get<int64_t>("vo_sp", n + 1),
           *sv = ar.get<int64_t>("vo_sv", n + 1);
-  // finished cells are kept from the count to the final arrays, but not under
-  // a workspace cap (1.2 KB a cell, where a call takes 156 bytes without):
-  // 3.1 ms less of a 131,071-cell grid's 6.2
-  VorKept *kept = ctx.ws.limit ? nullptr : ar.get<VorKept>("vo_kept", n);
+  // Finished cells are kept from the count to the final arrays: 3.1 ms less of
+  // a 131,071-cell grid's 6.2.  They take 1.2 KB a cell where a call takes 156
+  // bytes without, in a block of the context's pool that goes back to it here;
+  // under a workspace cap, and where memory is short, every cell is built again.
+  Arena keep;
+  keep.pool = &ctx.pool;
+  VorKept *kept = ctx.ws.limit ? nullptr : keep.get_if<VorKept>("vo_kept", n);
   int32_t *list = kept ? (int32_t *)ar.get<uint32_t>("vo_key", n) : nullptr;  // the sort's keys are spent
   {
     KernelTimer kt(&ctx, "voronoi_count", s);
@@ -1114,12 +1117,24 @@ void voronoi_build(Ctx &ctx, TessDev &t, int64_t n, const double *d_gen, const d
     size = std::max(size, hi[a] - lo[a]);
   }
   t.box_size = size * (1.0 + 1e-12);
-  t.gen = t.mem.get<double>("gen", 3 * n);
-  t.vert = t.mem.get<double>("vert", 3 * std::max<int64_t>(V, 1));
-  t.cell_face_off = t.mem.get<int64_t>("cfo", n + 1);
-  t.face_vtx_off = t.mem.get<int64_t>("fvo", F + 1);
-  t.face_vtx = t.mem.get<int32_t>("fv", std::max<int64_t>(FV, 1));
-  t.face_nbr = t.mem.get<int32_t>("fnbr", std::max<int64_t>(F, 1));
+  const auto arrays = [&] {
+    t.gen = t.mem.get<double>("gen", 3 * n);
+    t.vert = t.mem.get<double>("vert", 3 * std::max<int64_t>(V, 1));
+    t.cell_face_off = t.mem.get<int64_t>("cfo", n + 1);
+    t.face_vtx_off = t.mem.get<int64_t>("fvo", F + 1);
+    t.face_vtx = t.mem.get<int32_t>("fv", std::max<int64_t>(FV, 1));
+    t.face_nbr = t.mem.get<int32_t>("fnbr", std::max<int64_t>(F, 1));
+  };
+  try {
+    arrays();
+  } catch (const Error &e) {
+    if (e.code != SPHMAP_ENOMEM || !kept) throw;
+    keep.pool = nullptr;  // the kept cells' memory goes back to the device
+    keep.release();
+    kept = nullptr;
+    list = nullptr;
+    arrays();
+  }
   {
     KernelTimer kt(&ctx, "voronoi_faces", s);
     if (kept) {
@@ -1140,6 +1155,7 @@ void voronoi_build(Ctx &ctx, TessDev &t, int64_t n, const double *d_gen, const d
   SPH_HIP(hipMemcpyAsync(t.gen, ga, 3 * n * sizeof(double), hipMemcpyDeviceToDevice, s));
   if (d_gen_out) SPH_HIP(hipMemcpyAsync(d_gen_out, ga, 3 * n * sizeof(double), hipMemcpyDeviceToDevice, s));
   vor_check(ctx, err, s);
+  keep.release(true);  // s was waited for
   tess_prepare(ctx, t, s);
 }
 

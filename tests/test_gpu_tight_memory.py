@@ -1,0 +1,93 @@
+"""Calls where device memory runs short: scratch that only makes a call faster
+is given up when it does not fit beside what the call needs, and blocks kept
+for later calls go back to the device first.  A test finds the least free
+memory with which a call is carried out (by halving, to 8 MB) and compares it
+with that of the same call by other means."""
+import ctypes
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+MB = 1 << 20
+
+
+def free_bytes():
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+class Hold:
+    """Device memory taken past torch's allocator: all but n_bytes (to 4 MB)."""
+
+    def __init__(self, n_bytes):
+        self.hip = ctypes.CDLL("libamdhip64.so")
+        self.blocks = []
+        while (more := free_bytes() - n_bytes) > 4 * MB:
+            p = ctypes.c_void_p()
+            assert self.hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(more - 2 * MB)) == 0
+            self.blocks.append(p)
+
+    def free(self):
+        for p in self.blocks:
+            self.hip.hipFree(p)
+        self.blocks = []
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    import paper_2410_15227_amd as pkg
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    pkg.Context(0).close()  # the runtime's own first allocations
+    hold = Hold(4096 * MB)  # most of the device once: it takes a second
+    yield pkg
+    hold.free()
+
+
+def least(pkg, call, most):
+    """The least free memory (within 8 MB, at most `most`) with which call(n_bytes)
+    succeeds; call leaves n_bytes free by itself."""
+    lo, hi = 0, most
+    while hi - lo > 8 * MB:
+        mid = (lo + hi) // 2
+        try:
+            call(mid)
+            hi = mid
+        except pkg.SphmapError as e:
+            assert e.code == -2, e  # SPHMAP_ENOMEM
+            lo = mid
+    print("   least free memory", hi >> 20, "MB", flush=True)
+    return hi
+
+
+def test_voronoi_without_room_for_kept_cells(pkg):
+    n = 60000
+    kept = n * 1232  # bytes of finished cells kept between the count and the arrays
+    print("case: voronoi in tight memory", n, flush=True)
+    g = torch.as_tensor(np.random.default_rng(2).random((n, 3)), device="cuda")
+    ctx = pkg.Context(0)
+    dt, _ = pkg.build_voronoi(ctx, g, n_lloyd=0)
+    want = dt.export()
+    dt.free()
+    ctx.close()
+
+    def call(cap, n_bytes):
+        ctx = pkg.Context(0, workspace_bytes=cap)
+        hold = Hold(n_bytes)
+        try:
+            dt, _ = pkg.build_voronoi(ctx, g, n_lloyd=0)
+            hold.free()
+            t = dt.export()
+            dt.free()
+        finally:
+            hold.free()
+            ctx.close()
+        assert np.array_equal(want.vertices, t.vertices) and np.array_equal(want.face_vtx, t.face_vtx)
+
+    # a context with a workspace cap keeps no cells
+    bare = least(pkg, lambda b: call(8 << 30, b), 1600 * MB)
+    assert least(pkg, lambda b: call(0, b), 1600 * MB) < bare + kept // 2
