@@ -326,7 +326,7 @@ int sphmap_tess_free(sphmap_ctx *ctx, sphmap_tess *tess) {
   if (!ctx || !tess) return SPHMAP_EINVAL;
   (void)hipSetDevice(ctx->c.device);
   (void)hipDeviceSynchronize();
-  if (tess->maker == ctx && tess->t.device == ctx->c.device) tess->t.mem.pool = &ctx->c.pool;
+  if (tess->maker == ctx && tess->t.device == ctx->c.device && !ctx->c.ws.limit) tess->t.mem.pool = &ctx->c.pool;
   delete tess;
   return SPHMAP_OK;
 }

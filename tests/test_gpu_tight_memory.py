@@ -91,3 +91,23 @@ def test_voronoi_without_room_for_kept_cells(pkg):
     # a context with a workspace cap keeps no cells
     bare = least(pkg, lambda b: call(8 << 30, b), 1600 * MB)
     assert least(pkg, lambda b: call(0, b), 1600 * MB) < bare + kept // 2
+
+
+def test_blocks_of_a_grid_freed_under_a_cap(pkg):
+    """A cap set after the grid was made: its blocks go to the device."""
+    print("case: grid freed under a cap set later", flush=True)
+    g = torch.as_tensor(np.random.default_rng(5).random((20000, 3)), device="cuda")
+    ctx = pkg.Context(0)
+    pkg.build_voronoi(ctx, g, n_lloyd=0)[0].free()
+    ctx.set_pool_limit(0)
+    ctx.set_pool_limit(8 << 30)
+    base = free_bytes()
+    dt, _ = pkg.build_voronoi(ctx, g, n_lloyd=0)
+    ctx.set_pool_limit(0)  # what the build itself gave back
+    ctx.set_pool_limit(8 << 30)
+    assert base - free_bytes() > 100 * MB
+    ctx.set_workspace_limit(8 << 30)
+    dt.free()
+    left = base - free_bytes()
+    ctx.close()
+    assert left < 8 * MB
