@@ -373,6 +373,10 @@ __device__ inline bool vcuts(const VorLds &L, const VorCell &C, double nx, doubl
   return cuts;
 }
 
+// A bisector farther than this cuts nothing, nor does any after it in the order
+// of binary32 distances: equal ones are up to 1.2e-7 apart.
+__device__ __forceinline__ double vreach(const VorCell &C, double eps) { return (C.R + eps) * (1.0 + 2e-7); }
+
 // Cut by the bisectors of one batch of candidates (lane: the vector to the
 // site, its distance and its index), nearest first.  With `test`, the planes
 // are first tested against every vertex, one candidate per lane, so that the
@@ -406,10 +410,7 @@ __device__ bool vbatch(VorLds &L, VorCell &C, bool cand, double ex, double ey, d
   for (int i = 0; i < nc; ++i) {
     const int l = __builtin_ctzll(ballot64(rank == i));
     const double dl = readlane_d(dd, l);
-    if (dl > C.R + eps) {
-      if (!ballot64(rank > i && !(dd > C.R + eps))) break;  // (where keys are equal a nearer one may follow)
-      continue;
-    }
+    if (dl > vreach(C, eps)) break;
     if (!vcut(L, C, readlane_d(nx, l), readlane_d(ny, l), readlane_d(nz, l), dl, __builtin_amdgcn_readlane(id, l), eps,
               lane, err))
       return false;
@@ -542,7 +543,6 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
   const int off = vscan_excl(cnt);
   const int tot = __builtin_amdgcn_readlane(off + cnt, 63);
   uint64_t best = ~0ull;
-  bool again = false;
   if (nearest) {
     // the home cell (lane 13 of the 27) first, for a tight bound
     const int home0 = __builtin_amdgcn_readlane(off, 13), home1 = home0 + __builtin_amdgcn_readlane(cnt, 13);
@@ -589,19 +589,16 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
       }
       const int l = __builtin_ctzll(todo);
       const double dl = readlane_d(dd, l);
-      if (dl > C.R + eps) break;
+      if (dl > vreach(C, eps)) break;
       if (!vcut(L, C, readlane_d(nx, l), readlane_d(ny, l), readlane_d(nz, l), dl, __builtin_amdgcn_readlane(j, l),
                 eps, lane, err))
         return false;
     }
-    // past the first that is too far only one with an equal key may cut: then
-    // all of them are tested again
-    again = (todo & ballot64(!(dd > C.R + eps))) != 0ull;
   }
   // the nearest are done with: what they left cuts nothing a second time
   // (tested again with the others: 18.1 ms in place of 17.2)
   uint64_t upto = 0ull;
-  if (nearest && !again) {
+  if (nearest) {
     if (tot <= 64) return true;
     upto = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best, 63) |
            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(best >> 32), 63) << 32);
