@@ -299,9 +299,9 @@ int sphmap_pairs_export(sphmap_ctx *ctx, const sphmap_pairs *pairs, int64_t *d_c
                         double *d_w, void *stream);
 /* Release a retained list (waits for the device first).  Its device blocks
    go to the context's pool, from which later retained lists and grids
-   allocate: a block of B bytes serves a request of more than B/2 and at
-   most B bytes, so repeated steps make no device allocation.  The pool keeps at most
-   one eighth of the device's memory by default (sphmap_set_pool_limit);
+   allocate: a block of B bytes serves a list's request of more than B/2 and
+   at most B bytes, and a grid's of more than 8 B/9, so repeated steps make
+   no device allocation.  The pool keeps at most one eighth of the device's memory by default (sphmap_set_pool_limit);
    blocks beyond the limit are freed, and all of them are freed before a
    device allocation that fails is retried, and by sphmap_destroy.  Free
    every retained list before destroying its context.  The blocks of a grid

@@ -61,6 +61,7 @@ std::unique_ptr<sphmap_tess> new_tess(sphmap_ctx *ctx) {
   std::unique_ptr<sphmap_tess> T(new sphmap_tess);
   if (!ctx->c.ws.limit) {
     T->t.mem.pool = &ctx->c.pool;
+    T->t.mem.close = true;
     T->maker = ctx;
   }
   return T;

@@ -45,16 +45,16 @@ struct Buffer {
 // next allocations of the same context (a caching allocator: repeated steps
 // make no hipMalloc or hipFree, which for the arrays of a 131,071-cell grid
 // took 4.9 of 19.8 ms a build, and 4.9 of 17.5 ms of a timestep that builds the
-// grid of a 200,003-particle cloud; MI355X).  take() hands out the smallest kept block of at
-// least `bytes` and under twice that; put() keeps a block while the kept
-// total stays within `cap` and returns it to the device otherwise.  Only
-// blocks that no queued work still uses may be put back.
+// grid of a 200,003-particle cloud; MI355X).  take() hands out the
+// smallest kept block of at least `bytes` and at most `most`; put() keeps a
+// block while the kept total stays within `cap` and returns it to the device
+// otherwise.  Only blocks that no queued work still uses may be put back.
 struct BlockPool {
   std::mutex mu;
   std::multimap<size_t, void *> blocks;
   size_t held = 0;
   size_t cap = 0;
-  void *take(size_t bytes, size_t &got);
+  void *take(size_t bytes, size_t most, size_t &got);
   void put(void *p, size_t bytes);
   bool set_cap(size_t bytes);  // whether more is kept
   void trim();  // frees the largest blocks until the kept total is within cap
@@ -73,11 +73,15 @@ struct Budget {
 // Grow-only device allocations keyed by purpose, owned by a context or a
 // handle.  get() never shrinks; contents are not preserved on growth.  With
 // a pool, first allocations come from it and release() gives the blocks
-// back to it.  With a budget, growth that would take the budget's holdings
+// back to it: blocks of under twice the request, or, with `close`, of at most
+// an eighth more (the bound that sphmap_estimate_footprint states for grids),
+// and sizes then go by eighths of powers of two, so that requests that differ
+// a little from step to step still find their block.  With a budget, growth that would take the budget's holdings
 // past its limit fails with SPHMAP_ENOMEM before anything is allocated.
 struct Arena {
   std::map<std::string, Buffer> bufs;
   BlockPool *pool = nullptr;
+  bool close = false;
   BlockPool *spare = nullptr;  // emptied, as the pool is, before an allocation that failed is retried
   Budget *budget = nullptr;
   // fixed-region mode: buffers are carved in turn (256-byte aligned) from

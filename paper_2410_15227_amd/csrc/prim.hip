@@ -5,10 +5,10 @@
 
 namespace sphmap {
 
-void *BlockPool::take(size_t bytes, size_t &got) {
+void *BlockPool::take(size_t bytes, size_t most, size_t &got) {
   std::lock_guard<std::mutex> lock(mu);
   auto it = blocks.lower_bound(bytes);
-  if (it == blocks.end() || it->first / 2 >= bytes) return nullptr;
+  if (it == blocks.end() || it->first > most) return nullptr;
   void *p = it->second;
   got = it->first;
   held -= got;
@@ -67,6 +67,11 @@ void *Arena::get(const std::string &name, size_t bytes) {
   }
   if (b.bytes < bytes) {
     size_t want = bytes + bytes / 8 + 256;
+    if (close) {
+      size_t step = 512;
+      while (step * 16 <= bytes) step *= 2;
+      want = (bytes + step - 1) / step * step;
+    }
     if (budget && budget->limit && budget->held - b.bytes + want > budget->limit) {
       budget->required = std::max(budget->required, budget->held - b.bytes + want);
       throw Error{SPHMAP_ENOMEM, "workspace limit of " + std::to_string(budget->limit) + " bytes exceeded by " + name +
@@ -79,7 +84,7 @@ void *Arena::get(const std::string &name, size_t bytes) {
     b.bytes = 0;
     if (pool) {
       size_t got = 0;
-      if (void *q = pool->take(want, got)) {
+      if (void *q = close ? pool->take(bytes, bytes + bytes / 8 + 512, got) : pool->take(want, 2 * want - 1, got)) {
         b.p = q;
         b.bytes = got;
         return b.p;

@@ -1082,6 +1082,7 @@ void voronoi_build(Ctx &ctx, TessDev &t, int64_t n, const double *d_gen, const d
   // under a workspace cap, and where memory is short, every cell is built again.
   Arena keep;
   keep.pool = &ctx.pool;
+  keep.close = true;
   VorKept *kept = ctx.ws.limit ? nullptr : keep.get_if<VorKept>("vo_kept", n);
   int32_t *list = kept ? (int32_t *)ar.get<uint32_t>("vo_key", n) : nullptr;  // the sort's keys are spent
   {

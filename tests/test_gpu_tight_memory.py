@@ -111,3 +111,33 @@ def test_blocks_of_a_grid_freed_under_a_cap(pkg):
     left = base - free_bytes()
     ctx.close()
     assert left < 8 * MB
+
+
+def held_by_grid(pkg, ctx, build, base):
+    """What the device lacks while a grid is there, its maker's pool emptied."""
+    dt = build()
+    ctx.set_pool_limit(0)
+    got = base - free_bytes()
+    ctx.set_pool_limit(8 << 30)
+    return dt, got
+
+
+def test_grids_stay_within_the_stated_footprint(pkg):
+    """sphmap_estimate_footprint bounds what a grid holds, also when it is made
+    from blocks that a larger grid gave back."""
+    print("case: footprint of a grid from the pool", flush=True)
+    rng = np.random.default_rng(3)
+    big, small = (torch.as_tensor(rng.random((n, 3)), device="cuda") for n in (30000, 16500))
+    ctx = pkg.Context(0)
+    for g in (big, small):  # the scratch reaches its size
+        pkg.build_voronoi(ctx, g, n_lloyd=0)[0].free()
+    ctx.set_pool_limit(0)
+    ctx.set_pool_limit(8 << 30)
+    base = free_bytes()
+    pkg.build_voronoi(ctx, big, n_lloyd=0)[0].free()
+    dt, got = held_by_grid(pkg, ctx, lambda: pkg.build_voronoi(ctx, small, n_lloyd=0)[0], base)
+    est = ctx.estimate_footprint(1, dt.export())["tessellation"]
+    dt.free()
+    ctx.close()
+    print("   holds", got >> 20, "MB, stated bound", est >> 20, "MB", flush=True)
+    assert got <= est
