@@ -255,6 +255,11 @@ int sphmap_tess_set_face_neighbours(sphmap_ctx *ctx, sphmap_tess *tess, const in
   if (!ctx || !tess) return SPHMAP_EINVAL;
   return guarded(ctx, [&] {
     sphmap::TessDev &t = tess->t;
+    struct Spare {  // the caller's pool gives way to this call's arrays
+      sphmap::Arena &a;
+      ~Spare() { a.spare = nullptr; }
+    } spare{t.mem};
+    t.mem.spare = &ctx->c.pool;
     hipStream_t s = as_stream(stream);
     int64_t n = 0;
     if (!h_face_nbr) {

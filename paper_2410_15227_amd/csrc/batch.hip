@@ -111,6 +111,13 @@ void batch_plan_build(Ctx &ctx, BatchPlan &B, double headroom, hipStream_t s) {
   }
   B.ev_fork = new_event();
   B.scratch.resize(nb);
+  // the context's pool gives way to the plan's buffers while it is made
+  const auto spare = [&](BlockPool *pool) {
+    B.mem.spare = pool;
+    for (auto &P : B.P) P->mem.spare = pool;
+    for (Arena &a : B.scratch) a.spare = pool;
+  };
+  spare(&ctx.pool);
   B.n_max.assign(nb, 1);
   for (int k = 0; k < B.n_inst; ++k) B.n_max[k % nb] = std::max(B.n_max[k % nb], B.pd[k].n);
   // per-instance device counts, overflow bits, the plan's flag, the table
@@ -178,6 +185,7 @@ void batch_plan_build(Ctx &ctx, BatchPlan &B, double headroom, hipStream_t s) {
   }
   SPH_HIP(hipStreamEndCapture(B.origin, &B.graph));
   SPH_HIP(hipGraphInstantiate(&B.exec, B.graph, nullptr, nullptr, 0));
+  spare(nullptr);
 }
 
 void batch_plan_run(Ctx &ctx, BatchPlan &B, hipStream_t s) {

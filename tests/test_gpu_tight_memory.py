@@ -141,3 +141,34 @@ def test_grids_stay_within_the_stated_footprint(pkg):
     ctx.close()
     print("   holds", got >> 20, "MB, stated bound", est >> 20, "MB", flush=True)
     assert got <= est
+
+
+@pytest.mark.parametrize("what", ["neighbours", "plan"])
+def test_pool_blocks_give_way(pkg, workloads, what):
+    """A freed grid's blocks in the pool are the device's again for whatever the
+    context allocates next."""
+    print("case: pool gives way to", what, flush=True)
+    n = 40000 if what == "neighbours" else 20000
+    pos, m, h, _ = workloads.make_cloud("uniform", n, seed=6)
+    tess = workloads.voronoi(pos)
+    x, mm, hh = (torch.as_tensor(a, device="cuda") for a in (pos, m, h))
+    ctx, hold = pkg.Context(0), None
+    try:
+        dt = ctx.upload(tess, neighbours=False)
+        pkg.map_particles_to_cells(ctx, dt, x, hh, mm)  # scratch
+        for d in [ctx.upload(tess) for _ in range(2)]:
+            d.free()
+        hold = Hold(4 * MB)
+        if what == "neighbours":
+            assert dt.set_face_neighbours(tess.face_nbr) > 0
+        else:
+            plan = pkg.BatchPlan(ctx, [dt], [x], [hh], [mm])
+            plan.run()
+            torch.cuda.synchronize()
+            plan.free()
+        hold.free()
+        dt.free()
+    finally:
+        if hold:
+            hold.free()
+        ctx.close()
