@@ -627,8 +627,9 @@ void kd_pseudo_build(Ctx &ctx, KdArgs &ka, hipStream_t s) {
         k_kd_size_flags<<<grid_of(n), 256, 0, s>>>(n, pxm, nop, l, N, flag);
         SPH_LAUNCH_CHECK();
         scan_exclusive_i64(ar, flag, scan, n, true, s);
+        // (in buffers that are filled after the build, as lv)
         const int64_t room = ctx.ws.limit ? nb : n;  // no growth between the launches of a run
-        int64_t *nch = ar.get<int64_t>("kd_nch", room + 1), *choff = ar.get<int64_t>("kd_choff", room + 1);
+        int64_t *nch = ar.get<int64_t>("kd_uflag", room + 1), *choff = ar.get<int64_t>("kd_uoff", room + 1);
         if (nb <= kKdOne) {
           k_kd_split<<<1, kKdOne, 0, s>>>(l, scan, N);
           SPH_LAUNCH_CHECK();

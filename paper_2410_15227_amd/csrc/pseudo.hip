@@ -1484,9 +1484,10 @@ void pseudo_build(Ctx &ctx, PseudoArgs &a, hipStream_t s) {
     const int d0 = (int)loff.size() - 2, d1 = std::min(d0 + run, o.max_depth + 1);
     int64_t nb = loff[d0 + 1] - loff[d0];
     for (int d = d0; d < d1; ++d, nb = std::min(8 * nb, n)) {
+      // (in buffers that are filled after the build: no scratch of their own)
       const int64_t room = ctx.ws.limit ? nb : n;  // no growth between the launches of a run
-      int64_t *nch = ar.get<int64_t>("ps_nch", room + 1);
-      int64_t *choff = ar.get<int64_t>("ps_choff", room + 1);
+      int64_t *nch = ar.get<int64_t>("ps_flag", room + 1);
+      int64_t *choff = ar.get<int64_t>("ps_uoff", room + 1);
       k_split<<<strided_blocks(8 * nb), 256, 0, s>>>(G.N, lv + 1 + d, nb, d, keys, o.leaf_max, o.max_depth, nch);
       SPH_LAUNCH_CHECK();
       scan_exclusive_i64(ar, nch, choff, nb, true, s);
