@@ -2240,7 +2240,7 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
     FaceRec *faces = ctx.arena.get<FaceRec>("flat_faces", waves * kEntryCap);
     const GiftPlan &G = *(const GiftPlan *)tab->gifts;
     int32_t *rtw = G.any ? ctx.arena.get<int32_t>("flat_rslot", waves * kEntryCap) : nullptr;
-    int32_t *next = ctx.arena.get<int32_t>("flat_next", 2);
+    int32_t *next = ctx.arena.get<int32_t>("flat_next", kCtrInts);  // work counters, redo count
     int64_t *redo = ctx.arena.get<int64_t>("flat_redo", std::max<int64_t>(total, 1));
     ExactInst *d_inst = (ExactInst *)tab->insts;
     // gift slots from this step's pair counts, within the planned capacity
