@@ -141,14 +141,15 @@ int sphmap_create(int32_t device, size_t workspace_bytes, sphmap_ctx **out) {
   ctx->c.ws.limit = workspace_bytes;
   ctx->c.arena.budget = &ctx->c.ws;
   ctx->c.arena.spare = &ctx->c.pool;
+  ctx->c.words.budget = &ctx->c.ws;
   int rc = guarded(ctx.get(), [&] {
     size_t free_b = 0, total_b = 0;
     SPH_HIP(hipMemGetInfo(&free_b, &total_b));
     (void)ctx->c.pool.set_cap(total_b / 8);
     // this device's address of the fixed scratch of the no-allocation entry point
     (void)sphmap::noalloc_scratch_init(device);
-    ctx->c.d_counters = ctx->c.arena.get<int64_t>("counters", 8);
-    ctx->c.d_status = ctx->c.arena.get<int>("status", 4);
+    ctx->c.d_counters = ctx->c.words.get<int64_t>("counters", 8);
+    ctx->c.d_status = ctx->c.words.get<int>("status", 4);
     SPH_HIP(hipMemset(ctx->c.d_counters, 0, 8 * sizeof(int64_t)));
     SPH_HIP(hipMemset(ctx->c.d_status, 0, 4 * sizeof(int)));
   });
@@ -634,17 +635,7 @@ int sphmap_set_workspace_limit(sphmap_ctx *ctx, size_t bytes) {
       SPH_HIP(hipDeviceSynchronize());
       if (C.scratch_pairs) C.scratch_pairs->mem.release();
       for (auto *P : C.scratch_batch) P->mem.release();
-      int64_t *ctr = C.d_counters;
-      int *st = C.d_status;
-      int64_t hc[8];
-      int hs[4];
-      SPH_HIP(hipMemcpy(hc, ctr, sizeof hc, hipMemcpyDeviceToHost));
-      SPH_HIP(hipMemcpy(hs, st, sizeof hs, hipMemcpyDeviceToHost));
       C.arena.release();
-      C.d_counters = C.arena.get<int64_t>("counters", 8);
-      C.d_status = C.arena.get<int>("status", 4);
-      SPH_HIP(hipMemcpy(C.d_counters, hc, sizeof hc, hipMemcpyHostToDevice));
-      SPH_HIP(hipMemcpy(C.d_status, hs, sizeof hs, hipMemcpyHostToDevice));
     }
   });
 }

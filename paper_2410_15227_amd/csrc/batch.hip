@@ -18,7 +18,9 @@
 // branches run side by side.  A list whose count passes its capacity is
 // emptied and flagged, so a replay never writes out of bounds; the caller
 // reads the flag with the per-instance counts after the step and makes a
-// new plan if it is set.  Every kernel is the ordinary path's, so results
+// new plan if it is set.  Everything the graph writes to belongs to the plan or
+// the caller, but for the context's status word, which stays where it is: the
+// context's scratch may grow or be given back between replays.  Every kernel is the ordinary path's, so results
 // equal the uncaptured call's bit for bit.
 #include <algorithm>
 #include <memory>
@@ -56,7 +58,7 @@ void join(BatchPlan &B, hipStream_t to) {
   }
 }
 
-struct Redirect {  // scratch requests of the enclosed work go to one branch's arena
+struct Redirect {  // scratch requests of the enclosed work go to an arena of the plan
   Ctx &c;
   Redirect(Ctx &cc, Arena *a) : c(cc) { c.arena.redirect = a; }
   ~Redirect() { c.arena.redirect = nullptr; }
@@ -76,7 +78,10 @@ void enqueue_step(Ctx &ctx, BatchPlan &B, hipStream_t s) {
   join(B, s);
   std::vector<ExactJob> jobs(B.n_inst);
   for (int k = 0; k < B.n_inst; ++k) jobs[k] = ExactJob{B.t[k], &B.pd[k], B.P[k].get()};
-  exact_integral_batch(ctx, jobs, SPHMAP_PREC_MIXED, s, &B.tab);
+  {
+    Redirect r(ctx, &B.mem);
+    exact_integral_batch(ctx, jobs, SPHMAP_PREC_MIXED, s, &B.tab);
+  }
   fork(B, s);
   for (int k = 0; k < B.n_inst; ++k) {
     const int b = k % nb;

@@ -130,6 +130,7 @@ struct Ctx {
   PairsDev *scratch_pairs = nullptr;  // pair list of calls that do not keep one
   Budget ws;                          // workspace cap over arena and scratch pair lists
   Arena arena;
+  Arena words;                        // the counters and the status word, held for the context's life
   std::string last_error;
   bool timing = false;
   bool counting = false;

@@ -2221,8 +2221,7 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   }
   if (tab) {
     // pair counts on the device (capacity mode): the table of pointers is
-    // already uploaded; one kernel fills in the counts and chunk offsets,
-    // and the persistent grid takes its full size
+    // already uploaded; one kernel fills in the counts and chunk offsets
     SPH_REQUIRE(precision == SPHMAP_PREC_MIXED, SPHMAP_EINVAL, "a device-counted batch runs the mixed path");
     const int n_inst = (int)jobs.size();
     k_exact_table<<<1, 64, 0, s>>>(n_inst, tab->np, (ExactInst *)tab->insts, tab->chunk0);
@@ -2235,7 +2234,9 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
       bpc = it->second.blocks_per_cu;
       pf = it->second.per_fetch;
     }
-    const int64_t grid = (int64_t)ctx.n_cu * std::min(bpc, ctx.exact_per_cu);
+    // (no more wavefronts than the capacities' chunks: the records are the plan's own)
+    const int64_t grid = std::min<int64_t>((int64_t)ctx.n_cu * std::min(bpc, ctx.exact_per_cu),
+                                           div_up(div_up(total, 64) + n_inst, kFlatWaves));
     const int64_t waves = grid * kFlatWaves;
     FaceRec *faces = ctx.arena.get<FaceRec>("flat_faces", waves * kEntryCap);
     const GiftPlan &G = *(const GiftPlan *)tab->gifts;
