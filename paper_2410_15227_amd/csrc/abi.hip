@@ -142,6 +142,8 @@ int sphmap_create(int32_t device, size_t workspace_bytes, sphmap_ctx **out) {
   ctx->c.arena.budget = &ctx->c.ws;
   ctx->c.arena.spare = &ctx->c.pool;
   ctx->c.words.budget = &ctx->c.ws;
+  ctx->c.records.budget = &ctx->c.ws;
+  ctx->c.records.spare = &ctx->c.pool;
   int rc = guarded(ctx.get(), [&] {
     size_t free_b = 0, total_b = 0;
     SPH_HIP(hipMemGetInfo(&free_b, &total_b));
@@ -636,6 +638,7 @@ int sphmap_set_workspace_limit(sphmap_ctx *ctx, size_t bytes) {
       if (C.scratch_pairs) C.scratch_pairs->mem.release();
       for (auto *P : C.scratch_batch) P->mem.release();
       C.arena.release();
+      if (!C.plans) C.records.release();
     }
   });
 }

@@ -19,8 +19,9 @@
 // emptied and flagged, so a replay never writes out of bounds; the caller
 // reads the flag with the per-instance counts after the step and makes a
 // new plan if it is set.  Everything the graph writes to belongs to the plan or
-// the caller, but for the context's status word, which stays where it is: the
-// context's scratch may grow or be given back between replays.  Every kernel is the ordinary path's, so results
+// the caller, but for the context's status word and the records of its Exact
+// launches, which stay where they are: the context's other scratch may grow or
+// be given back between replays.  Every kernel is the ordinary path's, so results
 // equal the uncaptured call's bit for bit.
 #include <algorithm>
 #include <memory>
@@ -98,6 +99,7 @@ void enqueue_step(Ctx &ctx, BatchPlan &B, hipStream_t s) {
 }  // namespace
 
 BatchPlan::~BatchPlan() {
+  if (ctx) --ctx->plans;
   exact_table_free(tab);
   if (exec) (void)hipGraphExecDestroy(exec);
   if (graph) (void)hipGraphDestroy(graph);
@@ -123,6 +125,8 @@ void batch_plan_build(Ctx &ctx, BatchPlan &B, double headroom, hipStream_t s) {
     for (Arena &a : B.scratch) a.spare = pool;
   };
   spare(&ctx.pool);
+  B.ctx = &ctx;
+  ++ctx.plans;
   B.n_max.assign(nb, 1);
   for (int k = 0; k < B.n_inst; ++k) B.n_max[k % nb] = std::max(B.n_max[k % nb], B.pd[k].n);
   // per-instance device counts, overflow bits, the plan's flag, the table

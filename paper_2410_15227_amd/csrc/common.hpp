@@ -131,6 +131,10 @@ struct Ctx {
   Budget ws;                          // workspace cap over arena and scratch pair lists
   Arena arena;
   Arena words;                        // the counters and the status word, held for the context's life
+  // Records of the Exact launches' resident wavefronts, which batch plans share:
+  // a plan takes them at their largest, and they stay while there is a plan.
+  Arena records;
+  int plans = 0;
   std::string last_error;
   bool timing = false;
   bool counting = false;
@@ -351,6 +355,7 @@ struct BatchPlan {
   ExactTable tab;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
+  Ctx *ctx = nullptr;  // once it counts among the context's plans
   BatchPlan() = default;
   BatchPlan(const BatchPlan &) = delete;
   BatchPlan &operator=(const BatchPlan &) = delete;

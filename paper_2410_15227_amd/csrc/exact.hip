@@ -2221,7 +2221,8 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   }
   if (tab) {
     // pair counts on the device (capacity mode): the table of pointers is
-    // already uploaded; one kernel fills in the counts and chunk offsets
+    // already uploaded; one kernel fills in the counts and chunk offsets,
+    // and the persistent grid takes its full size
     SPH_REQUIRE(precision == SPHMAP_PREC_MIXED, SPHMAP_EINVAL, "a device-counted batch runs the mixed path");
     const int n_inst = (int)jobs.size();
     k_exact_table<<<1, 64, 0, s>>>(n_inst, tab->np, (ExactInst *)tab->insts, tab->chunk0);
@@ -2234,13 +2235,11 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
       bpc = it->second.blocks_per_cu;
       pf = it->second.per_fetch;
     }
-    // (no more wavefronts than the capacities' chunks: the records are the plan's own)
-    const int64_t grid = std::min<int64_t>((int64_t)ctx.n_cu * std::min(bpc, ctx.exact_per_cu),
-                                           div_up(div_up(total, 64) + n_inst, kFlatWaves));
-    const int64_t waves = grid * kFlatWaves;
-    FaceRec *faces = ctx.arena.get<FaceRec>("flat_faces", waves * kEntryCap);
+    const int64_t grid = (int64_t)ctx.n_cu * std::min(bpc, ctx.exact_per_cu);
+    const int64_t most = (int64_t)ctx.n_cu * ctx.exact_per_cu * kFlatWaves;  // so that they never grow
+    FaceRec *faces = ctx.records.get<FaceRec>("flat_faces", most * kEntryCap);
     const GiftPlan &G = *(const GiftPlan *)tab->gifts;
-    int32_t *rtw = G.any ? ctx.arena.get<int32_t>("flat_rslot", waves * kEntryCap) : nullptr;
+    int32_t *rtw = G.any ? ctx.records.get<int32_t>("flat_rslot", most * kEntryCap) : nullptr;
     int32_t *next = ctx.arena.get<int32_t>("flat_next", kCtrInts);  // work counters, redo count
     int64_t *redo = ctx.arena.get<int64_t>("flat_redo", std::max<int64_t>(total, 1));
     ExactInst *d_inst = (ExactInst *)tab->insts;
@@ -2307,8 +2306,10 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   int32_t *next = ctx.arena.get<int32_t>("flat_next", kCtrInts);  // work counters, redo count
   int64_t *redo = ctx.arena.get<int64_t>("flat_redo", total);
   if (fp64) {
-    const int64_t grid = std::min<int64_t>((int64_t)n_cu * ctx.exact64_per_cu, div_up(n_chunks, kFlatWaves));
-    FaceRec64 *faces = ctx.arena.get<FaceRec64>("flat_faces", grid * kFlatWaves * Geo64::kEntries);
+    // (never more than the mixed path's records: a plan may hold them)
+    static_assert(Geo64::kEntries * sizeof(FaceRec64) <= kEntryCap * sizeof(FaceRec), "a region of either");
+    const int64_t grid = std::min<int64_t>((int64_t)n_cu * std::min(ctx.exact64_per_cu, per_cu), div_up(n_chunks, kFlatWaves));
+    FaceRec64 *faces = ctx.records.get<FaceRec64>("flat_faces", grid * kFlatWaves * Geo64::kEntries);
     k_zero_i32<<<1, 64, 0, s>>>(next, kCtrInts);
     SPH_LAUNCH_CHECK();
     KernelTimer kt(&ctx, "exact_integral", s);
@@ -2323,8 +2324,8 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   auto launch = [&](int blocks_per_cu, int per_fetch) {
     const int64_t grid = std::min<int64_t>((int64_t)n_cu * std::min(blocks_per_cu, per_cu), div_up(n_chunks, kFlatWaves));
     const int64_t waves = grid * kFlatWaves;
-    FaceRec *faces = ctx.arena.get<FaceRec>("flat_faces", waves * kEntryCap);
-    int32_t *rtw = shared ? ctx.arena.get<int32_t>("flat_rslot", waves * kEntryCap) : nullptr;
+    FaceRec *faces = ctx.records.get<FaceRec>("flat_faces", waves * kEntryCap);
+    int32_t *rtw = shared ? ctx.records.get<int32_t>("flat_rslot", waves * kEntryCap) : nullptr;
     KernelTimer kz(&ctx, "flat_reset", s);
     k_zero_i32<<<1, 64, 0, s>>>(next, kCtrInts);
     SPH_LAUNCH_CHECK();
