@@ -51,6 +51,7 @@ inline hipStream_t as_stream(void *s) { return (hipStream_t)s; }
 sphmap_pairs *new_pairs(sphmap::Ctx &C) {
   sphmap_pairs *q = new sphmap_pairs;
   q->p.mem.pool = &C.pool;
+  q->p.mem.lender = &C.arena;
   return q;
 }
 
@@ -77,6 +78,7 @@ sphmap::PairsDev *scratch_pairs(sphmap::Ctx &C) {
     C.scratch_pairs = new sphmap::PairsDev;
     C.scratch_pairs->mem.budget = &C.ws;
     C.scratch_pairs->mem.spare = &C.pool;
+    C.scratch_pairs->mem.lender = &C.arena;
   }
   return C.scratch_pairs;
 }
@@ -144,6 +146,7 @@ int sphmap_create(int32_t device, size_t workspace_bytes, sphmap_ctx **out) {
   ctx->c.words.budget = &ctx->c.ws;
   ctx->c.records.budget = &ctx->c.ws;
   ctx->c.records.spare = &ctx->c.pool;
+  ctx->c.arena.lender = &ctx->c.records;
   int rc = guarded(ctx.get(), [&] {
     size_t free_b = 0, total_b = 0;
     SPH_HIP(hipMemGetInfo(&free_b, &total_b));
@@ -453,6 +456,7 @@ int map_particles_to_cells_batch(sphmap_ctx *ctx, int32_t n_inst, const sphmap_t
         C.scratch_batch.push_back(new sphmap::PairsDev);
         C.scratch_batch.back()->mem.budget = &C.ws;
         C.scratch_batch.back()->mem.spare = &C.pool;
+        C.scratch_batch.back()->mem.lender = &C.arena;
       }
       for (int k = 0; k < n_inst; ++k) P[k] = C.scratch_batch[k];
     }

@@ -39,6 +39,7 @@ struct Error {
 struct Buffer {
   void *p = nullptr;
   size_t bytes = 0;
+  bool spent = false;  // nothing of it is needed before the next request for it
 };
 
 // Device blocks given back by freed pair lists and grids, kept by size for the
@@ -82,7 +83,10 @@ struct Arena {
   std::map<std::string, Buffer> bufs;
   BlockPool *pool = nullptr;
   bool close = false;
-  BlockPool *spare = nullptr;  // emptied, as the pool is, before an allocation that failed is retried
+  // before an allocation that failed is retried: emptied, as the pool is, and
+  // the arena whose spent buffers are freed beside its own, and so on
+  BlockPool *spare = nullptr;
+  Arena *lender = nullptr;
   Budget *budget = nullptr;
   // fixed-region mode: buffers are carved in turn (256-byte aligned) from
   // [region, region + region_cap); nothing is allocated or freed, and a
@@ -106,6 +110,10 @@ struct Arena {
       return nullptr;
     }
   }
+  // The named buffer has served the current call (work that uses it may be
+  // queued): freed where an allocation fails, taken anew by the next request.
+  void spent(const std::string &name);
+  bool drop_spent();  // whether there was one
   // idle: no queued work uses the blocks, which a pool then takes without a wait
   void release(bool idle = false);
   ~Arena() { release(); }

@@ -2304,15 +2304,23 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   const int n_cu = ctx.n_cu, per_cu = ctx.exact_per_cu;
   const int64_t n_chunks = c0[n_inst];
   int32_t *next = ctx.arena.get<int32_t>("flat_next", kCtrInts);  // work counters, redo count
-  int64_t *redo = ctx.arena.get<int64_t>("flat_redo", total);
   if (fp64) {
     // (never more than the mixed path's records: a plan may hold them)
     static_assert(Geo64::kEntries * sizeof(FaceRec64) <= kEntryCap * sizeof(FaceRec), "a region of either");
     const int64_t grid = std::min<int64_t>((int64_t)n_cu * std::min(ctx.exact64_per_cu, per_cu), div_up(n_chunks, kFlatWaves));
-    FaceRec64 *faces = ctx.records.get<FaceRec64>("flat_faces", grid * kFlatWaves * Geo64::kEntries);
+    // (where these do not fit, the one-lane kernel needs neither)
+    int64_t *redo = ctx.arena.get_if<int64_t>("flat_redo", total);
+    FaceRec64 *faces = redo ? ctx.records.get_if<FaceRec64>("flat_faces", grid * kFlatWaves * Geo64::kEntries) : nullptr;
+    ctx.arena.spent("flat_redo");  // given back where what follows does not fit
+    if (!ctx.plans) ctx.records.spent("flat_faces");
+    KernelTimer kt(&ctx, "exact_integral", s);
+    if (!faces) {
+      exact_fp64_direct(jobs, nullptr, s);
+      kt.done();
+      return;
+    }
     k_zero_i32<<<1, 64, 0, s>>>(next, kCtrInts);
     SPH_LAUNCH_CHECK();
-    KernelTimer kt(&ctx, "exact_integral", s);
     k_exact_edges<Geo64, false><<<(unsigned)grid, 64 * kFlatWaves, 0, s>>>(d_inst, d_c0, n_inst, 1, nullptr, faces,
                                                                           nullptr, next, redo, next + kRedoCtr);
     SPH_LAUNCH_CHECK();
@@ -2321,6 +2329,7 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
     kt.done();
     return;
   }
+  int64_t *redo = ctx.arena.get<int64_t>("flat_redo", total);
   auto launch = [&](int blocks_per_cu, int per_fetch) {
     const int64_t grid = std::min<int64_t>((int64_t)n_cu * std::min(blocks_per_cu, per_cu), div_up(n_chunks, kFlatWaves));
     const int64_t waves = grid * kFlatWaves;

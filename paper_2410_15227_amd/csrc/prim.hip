@@ -54,6 +54,7 @@ bool BlockPool::release() {
 void *Arena::get(const std::string &name, size_t bytes) {
   if (redirect) return redirect->get(name, bytes);
   Buffer &b = bufs[name];
+  b.spent = false;
   if (region) {
     if (b.bytes >= bytes) return b.p;
     const size_t off = (region_used + 255) & ~(size_t)255;
@@ -95,6 +96,9 @@ void *Arena::get(const std::string &name, size_t bytes) {
     if (e != hipSuccess) (void)hipGetLastError();
     // the kept blocks first go back to the device
     if (e != hipSuccess && kept && kept->release()) e = hipMalloc(&b.p, want);
+    if (e != hipSuccess) (void)hipGetLastError();
+    // then what a part of this call is done with
+    if (e != hipSuccess && drop_spent()) e = hipMalloc(&b.p, want);
     if (e != hipSuccess) {
       b.p = nullptr;
       b.bytes = 0;
@@ -105,6 +109,26 @@ void *Arena::get(const std::string &name, size_t bytes) {
     if (budget) budget->held += want;
   }
   return b.p;
+}
+
+void Arena::spent(const std::string &name) {
+  if (redirect) return redirect->spent(name);
+  auto it = bufs.find(name);
+  if (it != bufs.end() && !region) it->second.spent = true;
+}
+
+bool Arena::drop_spent() {
+  bool any = false;
+  for (auto &kv : bufs) {
+    Buffer &b = kv.second;
+    if (!b.spent || !b.p) continue;
+    (void)hipFree(b.p);  // waits for queued work that uses it
+    if (budget) budget->held -= b.bytes;
+    b = Buffer();
+    any = true;
+  }
+  if (lender && lender->drop_spent()) any = true;
+  return any;
 }
 
 void Arena::release(bool idle) {

@@ -172,3 +172,33 @@ def test_pool_blocks_give_way(pkg, workloads, what):
         if hold:
             hold.free()
         ctx.close()
+
+
+def test_binary64_mapping_without_room_for_records(pkg, workloads):
+    """The binary64 edge kernel's face records (400 MB and more) are given up:
+    the call needs what the one-lane kernel of a capped context needs."""
+    print("case: binary64 mapping in tight memory", flush=True)
+    pos, m, h, _ = workloads.make_cloud("uniform", 20000, seed=6)
+    tess = workloads.voronoi(pos)
+    x, mm, hh = (torch.as_tensor(a, device="cuda") for a in (pos, m, h))
+    out = {k: torch.empty(tess.n_cells, dtype=torch.float64, device="cuda") for k in ("out_mass", "out_density")}
+    mass = {}
+
+    def call(cap, n_bytes):
+        ctx, hold = pkg.Context(0, workspace_bytes=cap), None
+        try:
+            dt = ctx.upload(tess)
+            hold = Hold(n_bytes)
+            pkg.map_particles_to_cells(ctx, dt, x, hh, mm, precision="fp64", with_coverage=False, **out)
+            torch.cuda.synchronize()
+            mass[cap] = out["out_mass"].clone()
+            hold.free()
+            dt.free()
+        finally:
+            if hold:
+                hold.free()
+            ctx.close()
+
+    bare = least(pkg, lambda b: call(64 << 30, b), 1200 * MB)
+    assert least(pkg, lambda b: call(0, b), 1200 * MB) < bare + 100 * MB
+    assert torch.allclose(mass[0], mass[64 << 30], rtol=1e-12, atol=0.0)
