@@ -742,6 +742,12 @@ constexpr int kWideTiles = 2048; // near tiles a workgroup of that kernel can ho
 constexpr int kWideWaves = 16;
 constexpr int kWideKept = 48;    // tiles whose terms it keeps
 constexpr int kNewtonSteps = 30;
+// Nodes up to which they take a workgroup each.  A chip holds 256 of those and
+// 4,096 and more single wavefronts: sets whose nodes all meet many units (h_fact
+// of 5 to 8) have 4,400 to 20,600 such nodes, and took 3.8 and 15.0 ms a build on
+// workgroups, 2.3 and 5.1 on wavefronts (k_hsolve_rest); the clouds of a million particles around
+// one source have 200 to 900, of which a few take 30 steps.
+constexpr int kWideNodes = 2048;
 
 // A node handed from the one-wave to the wide Newton kernel.
 struct WideNode {
@@ -754,6 +760,37 @@ struct WideNode {
 // 1 / he is finite).  Shorter ones, of nodes at the corner of the box, take
 // the binary64 sums.
 constexpr double kLeast32 = 1e-11;
+
+// One wavefront's Newton steps it, it + 1, ... from h with unit-order sums (hb:
+// 64 entries of LDS).  0: converged at h; -1: failed; 2: left, where `leave(h)`
+// says so, before step it from h.
+template <class Leave>
+__device__ __forceinline__ int newton_wave(const HUnits &U, int32_t e, double ax, double ay, double az, double h0,
+                                           double hfact, double eps, double2 *hb, Leave leave, int &it, double &h) {
+  for (; it < kNewtonSteps; ++it) {
+    if (leave(h)) return 2;
+    double sw, sd, hn = h;
+    int64_t nhit;
+    hsums<16>(U, e, ax, ay, az, h, false, 0, 1, hb, sw, sd, nhit);
+    const int v = newton_step(sw, sd, h, h0, hfact, eps, hn);
+    if (v < 0) return -1;
+    h = hn;
+    if (v > 0) return 0;
+  }
+  return -1;
+}
+// What becomes of entry e (one lane a node): h, or the bracket's list.
+__device__ __forceinline__ void newton_done(int32_t e, int branch, double h, double *o_h, int32_t *o_branch,
+                                            unsigned long long *bcount, int32_t *fails, int32_t *n_fails) {
+  if ((threadIdx.x & 63) != 0) return;
+  if (branch < 0) {
+    fails[atomicAdd(n_fails, 1)] = e;
+  } else {
+    o_h[e] = h;
+    if (o_branch) o_branch[e] = branch;
+    atomicAdd(&bcount[branch], 1ull);
+  }
+}
 
 constexpr int kHWaves = 4;    // pseudo-particles per workgroup in the Newton kernel
 constexpr int kBWaves = 16;   // wavefronts per pseudo-particle in the bracket kernel
@@ -784,45 +821,26 @@ __global__ void __launch_bounds__(64 * kHWaves) k_hsolve_newton(int64_t np, cons
   double hres = h0;
   int branch = 3;
   if (np <= bypass) {
-    branch = -1;  // failed unless a step converges
-    double h = h0;
     const int64_t nt = (U.nu + 63) >> 6;
-    for (int it = 0; it < kNewtonSteps; ++it) {
-      if (wide && U.n_mid == 0 && nt > kNearTiles) {
-        const double ih = 1.0 / h;
-        int near = 0;
-        for (int64_t b = 0; b < nt && near <= kNearTiles; b += 64) {
-          if (box_beyond(U.blo[b >> 6], U.bhi[b >> 6], ax, ay, az, ih)) continue;  // the same in every lane
-          const int64_t t = min(b + lane, nt - 1);
-          near += __popcll(__ballot(b + lane < nt && !box_beyond(U.tlo[t], U.thi[t], ax, ay, az, ih)));
-        }
-        if (near > kNearTiles) {
-          if (lane == 0) wide[atomicAdd(n_wide, 1)] = WideNode{e, it, h};
-          return;
-        }
+    int it = 0;
+    const auto near_many = [&](double h) {
+      if (!wide || U.n_mid != 0 || nt <= kNearTiles) return false;
+      const double ih = 1.0 / h;
+      int near = 0;
+      for (int64_t b = 0; b < nt && near <= kNearTiles; b += 64) {
+        if (box_beyond(U.blo[b >> 6], U.bhi[b >> 6], ax, ay, az, ih)) continue;  // the same in every lane
+        const int64_t t = min(b + lane, nt - 1);
+        near += __popcll(__ballot(b + lane < nt && !box_beyond(U.tlo[t], U.thi[t], ax, ay, az, ih)));
       }
-      double sw, sd, hn = h;
-      int64_t nhit;
-      hsums<16>(U, e, ax, ay, az, h, false, 0, 1, hbuf[threadIdx.x >> 6], sw, sd, nhit);
-      const int v = newton_step(sw, sd, h, h0, hfact, eps, hn);
-      if (v < 0) break;
-      if (v > 0) {
-        hres = hn;
-        branch = 0;
-        break;
-      }
-      h = hn;
+      return near > kNearTiles;
+    };
+    branch = newton_wave(U, e, ax, ay, az, h0, hfact, eps, hbuf[threadIdx.x >> 6], near_many, it, hres);
+    if (branch == 2) {
+      if (lane == 0) wide[atomicAdd(n_wide, 1)] = WideNode{e, it, hres};
+      return;
     }
   }
-  if (lane == 0) {
-    if (branch < 0) {
-      fails[atomicAdd(n_fails, 1)] = e;
-    } else {
-      o_h[e] = hres;
-      if (o_branch) o_branch[e] = branch;
-      atomicAdd(&bcount[branch], 1ull);
-    }
-  }
+  newton_done(e, branch, hres, o_h, o_branch, bcount, fails, n_fails);
 }
 
 // v of the lane a DPP control names, 0 where it names none; row_shr 1, 2, 4, 8
@@ -912,6 +930,7 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   constexpr int16_t kMarked = -32768;
   const int64_t nt = (U.nu + 63) >> 6;
+  if (*n_wide > kWideNodes) return;  // k_hsolve_rest takes them
   for (int b = blockIdx.x; b < *n_wide; b += gridDim.x) {
     const WideNode nd = wide[b];
     const double ax = o_xyz[3 * (int64_t)nd.e], ay = o_xyz[3 * (int64_t)nd.e + 1], az = o_xyz[3 * (int64_t)nd.e + 2];
@@ -1143,6 +1162,27 @@ __global__ void __launch_bounds__(64 * kWideWaves) k_hsolve_wide(const WideNode 
         fails[atomicAdd(n_fails, 1)] = nd.e;
       }
     }
+  }
+}
+
+// The nodes handed over, more of them than kWideNodes: a wavefront each, from
+// where the Newton kernel left them.
+__global__ void __launch_bounds__(64 * kHWaves) k_hsolve_rest(const WideNode *wide, const int32_t *n_wide, HUnits U,
+                                                             const double *o_xyz, const double *o_s, double hfact,
+                                                             double eps, double *o_h, int32_t *o_branch,
+                                                             unsigned long long *bcount, int32_t *fails,
+                                                             int32_t *n_fails) {
+  __shared__ double2 hbuf[kHWaves][64];
+  const int wid = threadIdx.x >> 6, n = *n_wide;
+  if (n <= kWideNodes) return;
+  for (int b = (int)blockIdx.x * kHWaves + wid; b < n; b += (int)gridDim.x * kHWaves) {
+    const WideNode nd = wide[b];
+    const double *x = o_xyz + 3 * (int64_t)nd.e;
+    double h = nd.h;
+    int it = nd.it;
+    const int branch = newton_wave(U, nd.e, x[0], x[1], x[2], hfact * 2.0 * o_s[nd.e], hfact, eps, hbuf[wid],
+                                   [](double) { return false; }, it, h);
+    newton_done(nd.e, branch, h, o_h, o_branch, bcount, fails, n_fails);
   }
 }
 
@@ -1413,8 +1453,9 @@ void node_hsolve(Ctx &ctx, int64_t np, const int32_t *plist, int64_t nu, const d
   int32_t *fails = ctx.arena.get<int32_t>("hs_fails", np);
   int32_t *n_fails = ctx.arena.get<int32_t>("hs_nfails", 2);
   int32_t *n_wide = n_fails + 1;
-  // (under a workspace cap every node stays with its wave: no new scratch)
-  WideNode *wide = ctx.ws.limit ? nullptr : ctx.arena.get<WideNode>("hs_wide", np);
+  // (under a workspace cap, and where memory is short, every node stays with its
+  // wave: no new scratch)
+  WideNode *wide = ctx.ws.limit ? nullptr : ctx.arena.get_if<WideNode>("hs_wide", np);
   k_fill_i32<<<1, 64, 0, s>>>(n_fails, 0, 2);
   SPH_LAUNCH_CHECK();
   const HUnits U{nu, upos, tlo, thi, blo, bhi, n_mid, mid_com, mid_u0, mid_u1, rcut};
@@ -1428,6 +1469,11 @@ void node_hsolve(Ctx &ctx, int64_t np, const int32_t *plist, int64_t nu, const d
     k_hsolve_wide<<<(unsigned)std::min<int64_t>(np, 1024), 64 * kWideWaves, 0, s>>>(
         wide, n_wide, U, o_xyz, o_s, hfact, eps, o_h, o_branch, bcount, fails, n_fails);
     SPH_LAUNCH_CHECK();
+    if (np > kWideNodes) {
+      k_hsolve_rest<<<(unsigned)div_up(np, kHWaves), 64 * kHWaves, 0, s>>>(wide, n_wide, U, o_xyz, o_s, hfact, eps,
+                                                                          o_h, o_branch, bcount, fails, n_fails);
+      SPH_LAUNCH_CHECK();
+    }
   }
   kt1.done();
   // one workgroup per node that Newton did not solve (the rest exit at
