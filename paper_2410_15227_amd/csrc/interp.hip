@@ -92,6 +92,14 @@ __device__ __forceinline__ float readlane_f(float v, int k) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
 }
 
+// Wavefronts to which few particles are spread, a power of two each.  The fewer
+// particles, the farther apart the 64 of a wavefront: its last walk then goes
+// through most of the set.  64, 1,024 and 8,192 scattered particles of 84,000 to
+// 93,000 entries took 0.95 to 2.2, 1.1 to 2.2 and 1.6 ms with 64 a wavefront
+// (0.4 to 1.0, 0.8 to 1.4 and 1.3 to 1.5 with a walk a particle); now 0.2, 0.23
+// and 0.31 (MI355X; 2,048 and 8,192 wavefronts are up to a third slower at
+// 65,536 and at 100,000 particles).
+constexpr int kInterpWaves = 4096;
 constexpr int kTurn = 2;    // balls a lane sums at a time
 constexpr int kGroups = 4;  // walks of a wave: the last takes all that is left
 template <int kNc>
@@ -104,12 +112,13 @@ struct InterpWave {
   uint32_t st[64 * kMaxLevels];     // node << 4 | level (a level-1 node index is below 2^27); 64 pushed a level
 };
 
-// One wavefront per 64 particles, components [c0, c0 + kNc) of ncomp.  The
-// particles around the first one left (within 2 h of its entry) share a walk:
-// the boxes of four nodes, or 64 balls, at a time are tested against the
-// group's box, boxes of balls also against its particles.  The balls that are
-// left are gathered in LDS, 64 at a time; each lane marks those that reach
-// its own particle and sums them.  The stack keeps boxes in ascending order,
+// One wavefront per `per` particles (64, fewer where that leaves less than
+// kInterpWaves wavefronts), components [c0, c0 + kNc) of ncomp.  The particles
+// around the first one left (within 2 h of its entry) share a walk: the boxes
+// of four nodes, or 64 balls, at a time are tested against the group's box,
+// boxes of balls also against its particles.  The balls that are left are
+// gathered in LDS, 64 at a time; each lane marks those that reach its own
+// particle and sums them.  The stack keeps boxes in ascending order,
 // so each sum runs over the balls r < 2 h in Morton order.
 // One thread a particle, with a walk and scattered loads of its own, took
 // 1.6 ms of 2.02 ms for 1,048,576 particles in three components, this takes
@@ -117,17 +126,17 @@ struct InterpWave {
 // for each ball that reaches a particle and as many for the walk, and for the
 // last third by the wavefronts around few particles of many small entries.
 template <int kNc>  // components of this pass
-__global__ void __launch_bounds__(64) k_interp(Hier H, const double4 *sd, int64_t n, const int32_t *qidx,
+__global__ void __launch_bounds__(64) k_interp(Hier H, const double4 *sd, int64_t n, int per, const int32_t *qidx,
                                                const double *xyz, const int64_t *owner, const double *eh,
                                                const int32_t *ekind, const double *val, int ncomp, int c0, double *out,
                                                int *status) {
 #pragma clang fp contract(off)
   __shared__ InterpWave<kNc> S;
   const int lane = threadIdx.x;
-  const int64_t t = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  const int64_t t = (int64_t)blockIdx.x * per + threadIdx.x;
   int64_t i = 0, o = 0;
   double px = 0.0, py = 0.0, pz = 0.0;
-  bool left = t < n;
+  bool left = lane < per && t < n;
   int bad = 0;
   if (left) {
     i = qidx[t];
@@ -380,18 +389,24 @@ void interpolate_particles(Ctx &ctx, int64_t n, const double *xyz, const int64_t
   H.sidx = sidx;
   build_hier(ar, sx, ne, 1e-6f, "ip", H, s);
 
-  // particles grouped by place
-  uint32_t *pkey = ar.get<uint32_t>("ip_pkey", n);
+  // particles grouped by place (no use where one batch holds every ball)
   int32_t *qidx = ar.get<int32_t>("ip_qidx", n);
-  k_place_keys<<<(unsigned)div_up(n, 256), 256, 0, s>>>(n, xyz, owner, ekind, pkey, qidx);
-  SPH_LAUNCH_CHECK();
-  radix_sort_u32(ar, pkey, qidx, n, kPlaceBits, s);
+  if (ne > 64) {
+    uint32_t *pkey = ar.get<uint32_t>("ip_pkey", n);
+    k_place_keys<<<(unsigned)div_up(n, 256), 256, 0, s>>>(n, xyz, owner, ekind, pkey, qidx);
+    SPH_LAUNCH_CHECK();
+    radix_sort_u32(ar, pkey, qidx, n, kPlaceBits, s);
+  } else {
+    iota_i32(qidx, n, s);
+  }
 
+  int per = 64;
+  while (per > 1 && div_up(n, per) < kInterpWaves) per /= 2;
   KernelTimer kt(&ctx, "interp", s);
   for (int c0 = 0; c0 < ncomp; c0 += kCompPass) {
     const int nc = std::min(kCompPass, ncomp - c0);
     const auto fn = nc == 1 ? k_interp<1> : nc == 2 ? k_interp<2> : nc == 3 ? k_interp<3> : k_interp<4>;
-    fn<<<(unsigned)div_up(n, 64), 64, 0, s>>>(H, sd, n, qidx, xyz, owner, eh, ekind, val, ncomp, c0, out,
+    fn<<<(unsigned)div_up(n, per), 64, 0, s>>>(H, sd, n, per, qidx, xyz, owner, eh, ekind, val, ncomp, c0, out,
                                               ctx.d_status);
     SPH_LAUNCH_CHECK();
   }
