@@ -565,8 +565,12 @@ __global__ void __launch_bounds__(256) k_exact_fp64(int64_t P, const int32_t *pa
 }
 
 // The pairs the binary64 edge kernel leaves: a particle on the cell's
-// boundary or within 1e-4 h of an edge's line, more than 64 faces or 256 candidate edges, or a term that is
-// not finite.
+// boundary or within 1e-4 h of an edge's line, more than 64 faces or 256
+// candidate edges, or a term that is not finite.  kListBlocks workgroups a CU,
+// as grids whose every pair is left here (cells of 96 faces, 1.2M pairs) need
+// the chip full: 33.5 ms with one, 27.1 with two, 24.7 now, as with one lane for
+// every pair from the start; a short list takes what it took.
+constexpr int kListBlocks = 16;
 __global__ void __launch_bounds__(256) k_exact_fp64_list(const int64_t *list, const int32_t *n_list,
                                                          const ExactInst *__restrict__ insts,
                                                          const int64_t *__restrict__ chunk0, int n_inst) {
@@ -2324,7 +2328,7 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
     k_exact_edges<Geo64, false><<<(unsigned)grid, 64 * kFlatWaves, 0, s>>>(d_inst, d_c0, n_inst, 1, nullptr, faces,
                                                                           nullptr, next, redo, next + kRedoCtr);
     SPH_LAUNCH_CHECK();
-    k_exact_fp64_list<<<(unsigned)n_cu, 256, 0, s>>>(redo, next + kRedoCtr, d_inst, d_c0, n_inst);
+    k_exact_fp64_list<<<(unsigned)(n_cu * kListBlocks), 256, 0, s>>>(redo, next + kRedoCtr, d_inst, d_c0, n_inst);
     SPH_LAUNCH_CHECK();
     kt.done();
     return;
