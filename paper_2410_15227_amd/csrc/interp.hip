@@ -74,8 +74,7 @@ __device__ inline uint32_t spread10(double x) {  // bit b of the cell number at 
   for (int b = 0; b < 10; ++b) r |= (v >> b & 1u) << (3 * b);
   return r;
 }
-__global__ void k_place_keys(int64_t n, const double *xyz, const int64_t *owner, const int32_t *ekind, uint32_t *key,
-                             int32_t *idx) {
+__global__ void k_place_keys(int64_t n, const double *xyz, uint32_t *key, int32_t *idx) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   key[i] = (spread10(xyz[3 * i]) | spread10(xyz[3 * i + 1]) << 1 | spread10(xyz[3 * i + 2]) << 2) >> (30 - kPlaceBits);
@@ -393,7 +392,7 @@ void interpolate_particles(Ctx &ctx, int64_t n, const double *xyz, const int64_t
   int32_t *qidx = ar.get<int32_t>("ip_qidx", n);
   if (ne > 64) {
     uint32_t *pkey = ar.get<uint32_t>("ip_pkey", n);
-    k_place_keys<<<(unsigned)div_up(n, 256), 256, 0, s>>>(n, xyz, owner, ekind, pkey, qidx);
+    k_place_keys<<<(unsigned)div_up(n, 256), 256, 0, s>>>(n, xyz, pkey, qidx);
     SPH_LAUNCH_CHECK();
     radix_sort_u32(ar, pkey, qidx, n, kPlaceBits, s);
   } else {

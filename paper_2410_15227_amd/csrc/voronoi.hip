@@ -71,7 +71,7 @@ constexpr int kErrVertices = 4;
 constexpr int kErrCycle = 8;
 constexpr int kErrOutside = 16;
 
-struct VorLds {  // 10,176 bytes: 4 workgroups a CU
+struct VorLds {  // 10,176 bytes: 16 workgroups of one wavefront a CU
   static constexpr int kP = kVP, kT = kVT;
   uint8_t T[kP][kP];              // vertex holding directed edge a -> b
   double vx[kT], vy[kT], vz[kT];  // vertex positions about the generator
@@ -378,13 +378,12 @@ __device__ inline bool vcuts(const VorLds &L, const VorCell &C, double nx, doubl
 __device__ __forceinline__ double vreach(const VorCell &C, double eps) { return (C.R + eps) * (1.0 + 2e-7); }
 
 // Cut by the bisectors of one batch of candidates (lane: the vector to the
-// site, its distance and its index), nearest first.  With `test`, the planes
-// are first tested against every vertex, one candidate per lane, so that the
-// many sites that no longer cut cost no serial step (a plane that cuts no
-// vertex cuts none of a smaller cell's).  Returns false on an error (bit in
-// err).
+// site, its distance and its index), nearest first.  The planes are first
+// tested against every vertex, one candidate per lane, so that the many sites
+// that no longer cut cost no serial step (a plane that cuts no vertex cuts none
+// of a smaller cell's).  Returns false on an error (bit in err).
 __device__ bool vbatch(VorLds &L, VorCell &C, bool cand, double ex, double ey, double ez, double dist,
-                       int32_t id, bool test, double eps, int lane, int &err) {
+                       int32_t id, double eps, int lane, int &err) {
   uint64_t cm = ballot64(cand);
   if (!cm) return true;
   if (ballot64(cand && !(dist > 0.0))) {
@@ -393,11 +392,9 @@ __device__ bool vbatch(VorLds &L, VorCell &C, bool cand, double ex, double ey, d
   }
   const double nx = ex / dist, ny = ey / dist, nz = ez / dist;
   const double dd = 0.5 * dist;
-  if (test) {
-    cand = vcuts(L, C, nx, ny, nz, dd, eps) && cand;
-    cm = ballot64(cand);
-    if (!cm) return true;
-  }
+  cand = vcuts(L, C, nx, ny, nz, dd, eps) && cand;
+  cm = ballot64(cand);
+  if (!cm) return true;
   const float key = (float)dist;
   int rank = 0;
   for (uint64_t m = cm; m; m &= m - 1) {
@@ -623,7 +620,7 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
         cand = j != c && vkey(dist, j) > upto;
       }
     }
-    if (!vbatch(L, C, cand, ex, ey, ez, dist, j, true, eps, lane, err)) return false;
+    if (!vbatch(L, C, cand, ex, ey, ez, dist, j, eps, lane, err)) return false;
     vsync();
   }
   return true;
