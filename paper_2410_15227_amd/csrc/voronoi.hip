@@ -95,8 +95,8 @@ struct VorLds {  // 10,176 bytes: 16 workgroups of one wavefront a CU
 
 // One cell, spread over a wavefront: vertex lane + 64 h in x[h], y[h], z[h],
 // tri[h] (planes a, b, c in bytes 0-2; a free slot has position 0, which no
-// bisector cuts); uniform: the live vertex slots, the plane count, and the
-// largest vertex distance.
+// bisector cuts); uniform: the live vertex slots, the plane count, and a bound
+// of the largest vertex distance.
 struct VorCell {
   static constexpr int kH = 2;
   double x[kH], y[kH], z[kH];
@@ -179,12 +179,16 @@ __device__ inline void vlink(VorLds &L, uint32_t tri, int t) {
   L.T[b][c] = (uint8_t)t;
   L.T[c][a] = (uint8_t)t;
 }
+// With room for the binary32 order of the sites: a bisector beyond R cuts
+// nothing, and nor does any after it, whose binary32 distance may be equal and
+// whose distance then up to 1.2e-7 smaller.
+constexpr double kVSlack = 1.0 + 2e-7;
 __device__ inline void vradius(VorCell &C) {
   double r2 = C.x[0] * C.x[0] + C.y[0] * C.y[0] + C.z[0] * C.z[0];
 #pragma unroll
   for (int h = 1; h < C.kH; ++h)
     if (C.live[h]) r2 = fmax(r2, C.x[h] * C.x[h] + C.y[h] * C.y[h] + C.z[h] * C.z[h]);
-  C.R = sqrt(vmaxd(r2));
+  C.R = sqrt(vmaxd(r2)) * kVSlack;
 }
 
 // Drop the planes no vertex lies on any more and renumber the rest.
@@ -373,10 +377,6 @@ __device__ inline bool vcuts(const VorLds &L, const VorCell &C, double nx, doubl
   return cuts;
 }
 
-// A bisector farther than this cuts nothing, nor does any after it in the order
-// of binary32 distances: equal ones are up to 1.2e-7 apart.
-__device__ __forceinline__ double vreach(const VorCell &C, double eps) { return (C.R + eps) * (1.0 + 2e-7); }
-
 // Cut by the bisectors of one batch of candidates (lane: the vector to the
 // site, its distance and its index), nearest first.  The planes are first
 // tested against every vertex, one candidate per lane, so that the many sites
@@ -407,7 +407,7 @@ __device__ bool vbatch(VorLds &L, VorCell &C, bool cand, double ex, double ey, d
   for (int i = 0; i < nc; ++i) {
     const int l = __builtin_ctzll(ballot64(rank == i));
     const double dl = readlane_d(dd, l);
-    if (dl > vreach(C, eps)) break;
+    if (dl > C.R + eps) break;
     if (!vcut(L, C, readlane_d(nx, l), readlane_d(ny, l), readlane_d(nz, l), dl, __builtin_amdgcn_readlane(id, l), eps,
               lane, err))
       return false;
@@ -586,7 +586,7 @@ __device__ bool vgroup(VorLds &L, VorCell &C, const RingGrid &Gd, int32_t c, dou
       }
       const int l = __builtin_ctzll(todo);
       const double dl = readlane_d(dd, l);
-      if (dl > vreach(C, eps)) break;
+      if (dl > C.R + eps) break;
       if (!vcut(L, C, readlane_d(nx, l), readlane_d(ny, l), readlane_d(nz, l), dl, __builtin_amdgcn_readlane(j, l),
                 eps, lane, err))
         return false;
