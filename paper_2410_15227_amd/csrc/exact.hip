@@ -574,8 +574,8 @@ constexpr int kListBlocks = 16;
 __global__ void __launch_bounds__(256) k_exact_fp64_list(const int64_t *list, const int32_t *n_list,
                                                          const ExactInst *__restrict__ insts,
                                                          const int64_t *__restrict__ chunk0, int n_inst) {
-  const int n = *n_list;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+  const int64_t n = *n_list;
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
     const int64_t gid = list[t];
     const int ins = inst_of(chunk0, n_inst, gid >> 6);
     const ExactInst &I = insts[ins];
@@ -2279,12 +2279,14 @@ void exact_integral_batch(Ctx &ctx, const std::vector<ExactJob> &jobs, int preci
   // kernel runs, which needs none, so that every call the cap admits stays
   // admitted: 41 against 8.0 ms for the 10.2M pairs of a 65,521-particle
   // turbulent cloud.  It also counts the work, and its weights are then
-  // replaced.
-  if (fp64 && (ctr || ctx.ws.limit)) {
+  // replaced.  A batch of 2^31 pairs, all of which may be left to the list,
+  // is past what that counts.
+  const bool direct = ctx.ws.limit || total >= ((int64_t)1 << 31);
+  if (fp64 && (ctr || direct)) {
     KernelTimer kt(&ctx, "exact_integral", s);
     exact_fp64_direct(jobs, ctr, s);
     kt.done();
-    if (ctx.ws.limit) return;
+    if (direct) return;
     ctr = nullptr;
   }
   // instance table: each instance's pairs start at a fresh 64-pair chunk
