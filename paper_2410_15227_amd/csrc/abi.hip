@@ -60,6 +60,7 @@ sphmap_pairs *new_pairs(sphmap::Ctx &C) {
 // frees it; between the two any context may use it, so it holds no pool.
 std::unique_ptr<sphmap_tess> new_tess(sphmap_ctx *ctx) {
   std::unique_ptr<sphmap_tess> T(new sphmap_tess);
+  T->t.mem.spare = &ctx->c.pool;
   if (!ctx->c.ws.limit) {
     T->t.mem.pool = &ctx->c.pool;
     T->t.mem.close = true;
@@ -68,7 +69,7 @@ std::unique_ptr<sphmap_tess> new_tess(sphmap_ctx *ctx) {
   return T;
 }
 sphmap_tess *made_tess(std::unique_ptr<sphmap_tess> &T) {
-  T->t.mem.pool = nullptr;
+  T->t.mem.pool = T->t.mem.spare = nullptr;
   return T.release();
 }
 

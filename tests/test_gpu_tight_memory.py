@@ -202,3 +202,27 @@ def test_binary64_mapping_without_room_for_records(pkg, workloads):
     bare = least(pkg, lambda b: call(64 << 30, b), 1200 * MB)
     assert least(pkg, lambda b: call(0, b), 1200 * MB) < bare + 100 * MB
     assert torch.allclose(mass[0], mass[64 << 30], rtol=1e-12, atol=0.0)
+
+
+def test_pool_gives_way_to_a_grid_under_a_cap(pkg, workloads):
+    """Blocks that lay in the pool before a cap was set are no use to a grid made
+    under it, but their memory is."""
+    print("case: pool gives way to a grid under a cap", flush=True)
+    pos, m, h, _ = workloads.make_cloud("uniform", 10000, seed=6)
+    tess = workloads.voronoi(pos)
+    ctx, hold = pkg.Context(0), None
+    try:
+        first = ctx.upload(tess)
+        for d in [ctx.upload(tess) for _ in range(2)]:
+            d.free()
+        ctx.set_workspace_limit(4 << 30)
+        hold = Hold(4 * MB)
+        dt = ctx.upload(tess)
+        assert all(torch.equal(a, b) for a, b in zip(dt.cell_info(), first.cell_info()))
+        hold.free()
+        dt.free()
+        first.free()
+    finally:
+        if hold:
+            hold.free()
+        ctx.close()
