@@ -77,7 +77,8 @@ int sphmap_version(void);
    grids are not part of the workspace. */
 int sphmap_create(int32_t device, size_t workspace_bytes, sphmap_ctx **out);
 /* Change the workspace cap (0 = none).  Lowering it below what the scratch
-   holds frees the scratch (after waiting for the device). */
+   holds frees the scratch (after waiting for the device), but for the part
+   that batch plans of the context share while there are any. */
 int sphmap_set_workspace_limit(sphmap_ctx *ctx, size_t bytes);
 /* Device bytes the scratch holds now, the cap, and the largest workspace a
    call refused with SPHMAP_ENOMEM since the cap was last set (0 if none);
@@ -107,7 +108,8 @@ int sphmap_sync_status(sphmap_ctx *ctx, void *stream, int32_t clear, int32_t *st
    n_pairs: the candidate-pair count when known (an earlier step on the same
    grid), else 0 for an estimate of 200 per particle.  Each named device
    buffer is counted as at least one 2 MiB allocation granule.  Caller
-   buffers are not included.  Errors: EINVAL for negative sizes. */
+   buffers are not included, nor is what the context's pool keeps.  Errors:
+   EINVAL for negative sizes. */
 typedef struct {
   size_t workspace;
   size_t pairs;
@@ -300,14 +302,14 @@ int sphmap_pairs_export(sphmap_ctx *ctx, const sphmap_pairs *pairs, int64_t *d_c
 /* Release a retained list (waits for the device first).  Its device blocks
    go to the context's pool, from which later retained lists and grids
    allocate: a block of B bytes serves a list's request of more than B/2 and
-   at most B bytes, and a grid's of more than 8 B/9, so repeated steps make
-   no device allocation.  The pool keeps at most one eighth of the device's memory by default (sphmap_set_pool_limit);
-   blocks beyond the limit are freed, and all of them are freed before a
-   device allocation that fails is retried, and by sphmap_destroy.  Free
-   every retained list before destroying its context.  The blocks of a grid
-   go to the pool of the context that made it when that context frees it
-   (sphmap_tess_free) and its workspace is not capped, to the device
-   otherwise. */
+   at most B bytes, and a grid's of at least 8/9 B, so repeated steps make
+   no device allocation.  The pool keeps at most one eighth of the device's
+   memory by default (sphmap_set_pool_limit); blocks beyond the limit are
+   freed, and all of them are freed before a device allocation of the context
+   that fails is retried, and by sphmap_destroy.  Free every retained list
+   before destroying its context.  The blocks of a grid go to the pool of the
+   context that made it when that context frees it (sphmap_tess_free) and its
+   workspace is not capped then, to the device otherwise. */
 int sphmap_pairs_free(sphmap_ctx *ctx, sphmap_pairs *pairs);
 /* Largest total of device memory, in bytes, that the context's pool of
    freed pair-list and grid blocks may keep (0: keep none).  Blocks held

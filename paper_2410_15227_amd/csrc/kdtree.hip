@@ -606,8 +606,8 @@ void kd_pseudo_build(Ctx &ctx, KdArgs &ka, hipStream_t s) {
   // empty and changes nothing.  A run of one level, as under a workspace cap,
   // knows its exact size, and takes no more scratch than that.
   // With every level's size waited for (45 us) and 13 launches a level where
-  // there are 7 to 10 now, builds of 262,139 and 8,000 particles took 2.69 and
-  // 1.64 ms; they take 2.12 and 1.15 (MI355X).
+  // there are 7 to 10 now, builds of 262,139 and 8,000 particles took 2.59 and
+  // 1.64 ms; they take 1.87 and 1.15 (MI355X).
   std::vector<int64_t> loff = {0, 1};
   {
     KernelTimer kt(&ctx, "kd_build", s);
